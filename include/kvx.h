@@ -308,15 +308,15 @@ typedef struct kvx_plan_slot {
  *   well-formed records (kvx_plan_pages returns both).  Read on the host to
  *   shape the launch.
  * When the records copy at least 64 KiB per destination page and layer on
- * average and both tables hold at most INT32_MAX entries, the call can
+ * average, or 12 KiB and two thirds of a page, and both tables hold 1 to
+ * INT32_MAX entries, the call can
  * sweep: one workgroup per 1 KiB piece of each destination page of each
  * layer, layer by layer and page by page, every page on one XCD, instead of
  * a persistent grid.  Started in that order by the hardware, the pieces in
  * flight stay within a small window that slides through the transfer; on
- * MI355X this holds the handoff's 256 KiB pages at 6.1-6.35 TB/s and MLA's
- * 72 KiB pages at 5.75-5.97 TB/s in every process, where the persistent grid
- * ranges from 5.1 to 6.4 TB/s with the physical placement of the pools
- * (for MLA above the sweep in most processes, 3-8% below it in others).
+ * MI355X this holds the handoff's 256 KiB pages at 6.55-6.65 TB/s and MLA's
+ * 72 KiB pages at 5.8-6.1 TB/s, where the persistent grid
+ * ranges from 5.1 to 6.4 TB/s with the physical placement of the pools.
  * Which of the two launches such a call takes follows
  * kvx_set_launch_choice(): by default the faster one on these pools, found
  * by timing both on the first calls.

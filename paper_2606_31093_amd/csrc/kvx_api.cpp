@@ -341,44 +341,29 @@ int check_slice(const kvx_slice &sl, const Shape &s, const Shape &d) {
 // group > 0 the layer range is moved in groups of `group` layers, one launch
 // each, and events[g] is recorded on the stream after group g.
 // A planned transfer whose shape the sweep kernel serves well gets its
-// launch: at least KVX_SWEEP_MIN_BYTES copied per destination page and layer
-// on average, page tables whose indices fit in int32, and a grid of at most
-// KVX_SWEEP_MAX_BLOCKS workgroups per pass.  Otherwise, and for unplanned
-// calls, the persistent grid.
+// launch: enough bytes copied per destination page and layer on average
+// (KVX_SWEEP_MIN_BYTES, KVX_SWEEP_MIN_DENSE_BYTES), page tables whose indices
+// fit in int32, and at most 2^31 page slots over all layers.  Otherwise, and
+// for unplanned calls, the persistent grid.
 void plan_sweep(kvx::Params &P, const void *plan, int64_t plan_pages, int64_t plan_tokens) {
     P.sweep = 0;
     if (!plan || plan_pages < 1 || plan_tokens < 1 || P.n_reqs < 1 || P.op != kvx::OP_TRANSFER) return;
-    if (P.src.pt_len > INT32_MAX || P.dst.pt_len > INT32_MAX) return;
-    // rows per head of a page's enumeration: a head-major destination takes
-    // whole blocks of slots, aligned to the page, so any slot range of a page
-    // covers at most its ceil(T / block) blocks
-    constexpr int64_t SB = KVX_SWEEP_SLOT_BLOCK;
-    const int64_t T = P.dst.T, rows_per_head = P.dst.tok_contig ? T : (T + SB - 1) / SB * SB;
+    if (P.src.pt_len > INT32_MAX || P.dst.pt_len > INT32_MAX || P.src.pt_len < 1 || P.dst.pt_len < 1) return;
     // average bytes copied per destination page and layer
     const int64_t token_bytes = (int64_t)P.C * P.H * P.row_bytes;
-    if (plan_tokens > INT64_MAX / token_bytes || plan_tokens * token_bytes < KVX_SWEEP_MIN_BYTES * plan_pages)
+    if (plan_tokens > INT64_MAX / token_bytes) return;
+    const int64_t avg = plan_tokens * token_bytes / plan_pages, full = token_bytes * P.dst.T;
+    if (avg < KVX_SWEEP_MIN_BYTES && (avg < KVX_SWEEP_MIN_DENSE_BYTES || 3 * avg < 2 * full)) return;
+    // page slots are numbered with 31 bits, and one page's pieces fit one launch
+    if (plan_pages > INT32_MAX / P.L) return;
+    constexpr int64_t SB = KVX_SWEEP_SLOT_BLOCK;
+    const int64_t page_slots = ((int64_t)P.dst.T + SB - 1) / SB * SB;
+    if (page_slots * P.C * P.H * P.vpr > INT32_MAX || kvx::sweep_pieces(P, page_slots) > KVX_SWEEP_MAX_BLOCKS)
         return;
-    // pieces of 64 vectors per page: the vectors of the page's enumeration
-    const int64_t tile_vecs = (int64_t)P.C * rows_per_head * P.H * P.vpr;
-    // workgroups per page: KVX_SWEEP_PIECES pieces each
-    const int64_t ppt = ((tile_vecs + 63) / 64 + KVX_SWEEP_PIECES - 1) / KVX_SWEEP_PIECES;
-    const int64_t per_slot = (int64_t)P.L * ppt;         // workgroups per page slot
-    if (per_slot > KVX_SWEEP_MAX_BLOCKS) return;
-    // page slots per pass: the plan's pages in KVX_SWEEP_PASSES passes (fewer
-    // for small pages), within the grid cap
-    const int64_t passes = plan_tokens * token_bytes < KVX_SWEEP_SMALL_BYTES * plan_pages
-                               ? KVX_SWEEP_PASSES_SMALL : KVX_SWEEP_PASSES;
-    const int64_t want = (plan_pages + passes - 1) / passes;
-    const int64_t slots = want < KVX_SWEEP_MAX_BLOCKS / per_slot ? want : KVX_SWEEP_MAX_BLOCKS / per_slot;
     P.sweep = 1;
     P.prefix = static_cast<const int64_t *>(plan);
     P.slots = reinterpret_cast<const kvx_plan_slot *>(P.prefix + P.n_reqs + 1);
     P.plan_pages = plan_pages;
-    P.sweep_pages = (int32_t)slots;
-    P.sweep_ppt = (uint32_t)ppt;
-    P.fd_ppt = kvx::make_fastdiv((uint32_t)ppt);
-    P.fd_sp = kvx::make_fastdiv((uint32_t)slots);
-    P.fd_hv = kvx::make_fastdiv((uint32_t)(P.H * P.vpr));
 }
 
 #ifndef KVX_LAUNCH_CHOICE_DEFAULT

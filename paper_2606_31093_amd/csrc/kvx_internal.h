@@ -16,35 +16,24 @@
 #ifndef KVX_SWEEP_SLOT_BLOCK
 #define KVX_SWEEP_SLOT_BLOCK 16
 #endif
-// A planned transfer sweeps when its records copy at least this many bytes
-// per destination page and layer on average (measured: from 72 KiB pages up
-// the sweep holds its rate in every placement of the pools, where the
-// persistent grid's varies by up to 20% between processes).
+// A planned transfer can sweep when its records copy at least this many bytes
+// per destination page and layer on average, or at least
+// KVX_SWEEP_MIN_DENSE_BYTES and two thirds of a page.  Measured against the
+// persistent grid on the same pools, full pages, TB/s read + write: 16 KiB
+// pages 5.16 to 5.02, 64 KiB 6.07 to 5.11, 128 KiB 6.64 to 5.1.  A sweep
+// launches a page's pieces whether or not the records copy them; an empty
+// one takes two thirds of a copied one's time, so a page less than two thirds
+// full is left to the grid unless it is large (there the measured launch
+// choice decides).
 #ifndef KVX_SWEEP_MIN_BYTES
 #define KVX_SWEEP_MIN_BYTES (64 << 10)
 #endif
-// Pieces of 64 vectors one sweep workgroup copies, one after the other.
-#ifndef KVX_SWEEP_PIECES
-#define KVX_SWEEP_PIECES 1
-#endif
-// Passes of a sweep launch over the plan's pages: each workgroup copies its
-// piece of one page in each pass, pages plan_pages / passes apart.  Measured:
-// 3 passes move 128-256 KiB pages 4-6% faster than 1; 2 passes beat 3 by
-// 0.5-1.5% at every page size tried from 64 to 108 KiB, where from 121 KiB
-// copied per page and layer on average up they vary from -4% to +1%.  So
-// below 96 KiB on average a launch takes 2.
-#ifndef KVX_SWEEP_PASSES
-#define KVX_SWEEP_PASSES 3
-#endif
-#ifndef KVX_SWEEP_SMALL_BYTES
-#define KVX_SWEEP_SMALL_BYTES (96 << 10)
-#endif
-#ifndef KVX_SWEEP_PASSES_SMALL
-#define KVX_SWEEP_PASSES_SMALL 2
+#ifndef KVX_SWEEP_MIN_DENSE_BYTES
+#define KVX_SWEEP_MIN_DENSE_BYTES (12 << 10)
 #endif
 // Most workgroups of one sweep launch: the work-items of a launch (64 per
-// workgroup) must stay below 2^32, and this keeps them below 2^31.  Beyond
-// it, workgroups loop over page slots.
+// workgroup) must stay below 2^32, and this keeps them below 2^31.  A larger
+// transfer takes several launches.
 #ifndef KVX_SWEEP_MAX_BLOCKS
 #define KVX_SWEEP_MAX_BLOCKS (INT32_MAX / 64)
 #endif
@@ -60,20 +49,21 @@ namespace kvx {
 struct FastDiv {
     uint32_t d;   // divisor, 1 <= d < 2^31
     uint32_t m;   // ceil(2^(31 + l) / d), l = ceil(log2 d); below 2^32
-    uint32_t sh;  // 31 + l
+    uint32_t l;
 };
 
 inline FastDiv make_fastdiv(uint32_t d) {
     uint32_t l = 0;
     while ((1ull << l) < d) ++l;
-    return FastDiv{d, (uint32_t)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
+    return FastDiv{d, (uint32_t)(((1ull << (31 + l)) + d - 1) / d), l};
 }
 
 // n / d for n < 2^31 without a branch: n * m / 2^(31 + l) = n / d + n * (m *
 // d - 2^(31 + l)) / (d * 2^(31 + l)), and the second term, below n / 2^(31 +
-// l) < 2^-l <= 1 / d, cannot reach the next multiple of 1 / d.
+// l) < 2^-l <= 1 / d, cannot reach the next multiple of 1 / d.  Taken as
+// 2n * m / 2^(32 + l): one 32-bit high product and a 32-bit shift.
 __host__ __device__ inline uint32_t fd_div(const FastDiv &f, uint32_t n) {
-    return (uint32_t)(((uint64_t)n * f.m) >> f.sh);
+    return (uint32_t)(((uint64_t)(n << 1) * f.m) >> 32) >> f.l;
 }
 
 // One side of a copy.  A pool side addresses row (l, page, c, slot, h) at
@@ -109,22 +99,20 @@ struct Params {
     int32_t dst_host;    // the destination is pinned host memory (plain stores)
     FastDiv fd_vpr, fd_H, fd_To;
     FastDiv fd_Tt;       // tiling side's page_tokens
-    // Sweep launch (a planned pool -> pool transfer): one workgroup per piece
-    // of 64 vectors of one destination page of one layer and pass.
-    // sweep_pages page slots per layer are launched (plan_pages / passes, or
-    // fewer when the grid is capped; workgroups go on to the slots
-    // sweep_pages apart), sweep_ppt pieces per page.  prefix[r] =
+    // Sweep launch (a planned pool -> pool transfer): prefix[r] =
     // destination pages of records 0..r-1, slots[q] = page q of the plan.
     // sweep == 0: persistent grid.
     int32_t sweep;
-    int32_t sweep_pages;
-    uint32_t sweep_ppt;
     int64_t plan_pages;
-    FastDiv fd_ppt, fd_sp;
-    FastDiv fd_hv;       // H * vpr: vectors per token of a token-major side
     const int64_t *prefix;
     const kvx_plan_slot *slots;
 };
+
+// Pieces (workgroups) of a page of page_slots slots in a sweep.
+inline uint32_t sweep_pieces(const Params &p, int64_t page_slots) {
+    const int64_t vecs = (int64_t)p.C * page_slots * p.H * p.vpr;
+    return (uint32_t)((vecs + 63) / 64);
+}
 
 // Launch on `stream`; returns a hipError_t value.
 int launch(const Params &p, hipStream_t stream);

@@ -454,135 +454,176 @@ __global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
 }
 
 // Lane k's row of a sweep piece: kv component c, slot, head h, vector v of
-// the row, in the vector order of copy_rows (a head-major destination in
-// blocks of KVX_SWEEP_SLOT_BLOCK slots); valid is cleared for a masked slot
-// of a head-major destination.
-template <bool TTHD>
-__device__ __forceinline__ void tile_row(const Params &p, uint32_t k, uint32_t rows_c, int32_t sa,
+// the row, in the vector order of copy_rows (TOKENS: token by token; else, for
+// a head-major destination, in blocks of KVX_SWEEP_SLOT_BLOCK slots); valid is
+// cleared for a masked slot of a head-major destination.
+template <bool TOKENS>
+__device__ __forceinline__ void tile_row(uint32_t H, uint32_t vpr, const FastDiv &fd_H,
+                                         const FastDiv &fd_vpr, uint32_t k, uint32_t rows_c, int32_t sa,
                                          int32_t sb, uint32_t blk0, uint32_t &c, uint32_t &slot,
                                          uint32_t &h, uint32_t &v, bool &valid) {
     constexpr uint32_t SB = KVX_SWEEP_SLOT_BLOCK;
-    const uint32_t rw = fd_div(p.fd_vpr, k);
-    v = k - rw * p.vpr;
+    const uint32_t rw = fd_div(fd_vpr, k);
+    v = k - rw * vpr;
     c = rw >= rows_c;
     const uint32_t rr = rw - c * rows_c;
-    if (TTHD) {
-        const uint32_t tt = fd_div(p.fd_H, rr);
-        h = rr - tt * p.H;
+    if (TOKENS) {
+        const uint32_t tt = fd_div(fd_H, rr);
+        h = rr - tt * H;
         slot = (uint32_t)sa + tt;
     } else {
         const uint32_t q1 = rr / SB;
-        const uint32_t blk = fd_div(p.fd_H, q1);
-        h = q1 - blk * p.H;
+        const uint32_t blk = fd_div(fd_H, q1);
+        h = q1 - blk * H;
         slot = (blk0 + blk) * SB + (rr - q1 * SB);
         valid = valid && slot >= (uint32_t)sa && slot < (uint32_t)sb;
     }
 }
 
-// One piece of the sweep: the vectors [kb, kb + 64) of destination page slot
-// d of layer l, one vector per lane, in the vector order of copy_rows (a
-// head-major destination in blocks of KVX_SWEEP_SLOT_BLOCK slots, the slots
-// outside the page's range masked).  Every load of metadata on the path that copies (the slot,
-// the destination page id, and the source page id when all the piece's rows
-// lie in one source page, the usual case) is uniform and comes before the
-// first store or atomic, so it goes through the scalar cache.  FLAT (both
-// sides token-major with every head): the page is C runs of contiguous
-// vectors on both sides, each lane finds its token's source page, and a
-// piece whose rows lie in one source page is a plain vector copy.  Errors
-// are reported for the positions the piece covers, destination first.  The
-// slot's fields are only trusted as far as keeping every access inside the
-// pools and tables; whether they match the records is checked separately
-// (slot_agrees).
-template <bool TTHD, bool FLAT, bool HOST>
-__device__ __forceinline__ void sweep_piece(const Params &p, const kvx_plan_slot &d, uint32_t l,
-                                            uint32_t kb) {
+// What the copying part of the sweep reads of its arguments.
+struct SweepArgs {
+    const kvx_plan_slot *slots;
+    FastDiv ppt;                 // pieces per page slot
+    FastDiv pages;               // page slots per layer: the plan's pages
+    uint32_t slot0, n_slots;     // page slots of this launch: [slot0, slot0 + n_slots) of layers x pages
+    uint32_t checks;             // leading workgroups that check the plan (a multiple of 8)
+    uint32_t general;            // nonzero: strides too large for the fields below
+    const int32_t *d_pt, *s_pt;
+    uint32_t d_last, s_last;     // last index of each page table
+    uint32_t d_T, s_T, d_lastp, s_lastp;   // slots per page, last page id
+    FastDiv fd_To;
+    FastDiv fd_hv;               // vectors of one token's copied heads
+    uint32_t C;
+    uint32_t d_t, s_t;           // bytes from one slot to the next
+    uint32_t d_c, s_c;           // bytes from K to V
+    uint32_t d_l, d_p, s_l, s_p; // 16-byte units from one layer or page to the next
+    char *d_base;
+    const char *s_base;
+    uint32_t H, vpr, d_h, s_h;   // rows only
+    FastDiv fd_H, fd_vpr;        // rows only
+};
+
+// How a piece's vectors lie on both sides:
+// - RUNS: the copied heads of consecutive tokens are one run on both sides;
+// - TOKENS: the copied heads of a token are one run on both sides;
+// - ROWS_T: token by token into a token-major destination, rows resolved;
+// - ROWS_H: by slot blocks into a head-major destination, rows resolved.
+enum SweepMode { RUNS, TOKENS, ROWS_T, ROWS_H };
+
+// A piece that the sweep's common path does not cover: rows in several source
+// pages, a page id or index out of range, or strides too large for 32-bit
+// fields.  Every lane resolves its own source page, and errors are
+// reported for the positions the piece covers, destination first.
+template <bool TOKEN_ORDER, bool HOST>
+__device__ __forceinline__ void sweep_piece_general(const Params &p, const kvx_plan_slot &d, uint32_t l,
+                                                    uint32_t kb) {
     const Side &ts = p.dst, &os = p.src;
     const int32_t sa = d.dst_slot, so_a = d.src_slot;
     const uint32_t ntok = (uint32_t)d.n_tokens;
-    if (!((uint32_t)sa < (uint32_t)ts.T && ntok - 1u < (uint32_t)(ts.T - sa) &&
-          (uint32_t)so_a < (uint32_t)os.T))
-        return;
     const int32_t sb = sa + (int32_t)ntok;
     constexpr uint32_t SB = KVX_SWEEP_SLOT_BLOCK;
     const uint32_t blk0 = (uint32_t)sa / SB, nblk = ((uint32_t)sb - 1) / SB - blk0 + 1;
-    const uint32_t rows_c = TTHD ? ntok * p.H : p.H * nblk * SB;
+    const uint32_t rows_c = TOKEN_ORDER ? ntok * p.H : p.H * nblk * SB;
     const uint32_t total = rows_c * p.vpr * (uint32_t)p.C;
-    if (kb >= total) return;
-    const uint32_t lane = threadIdx.x;
-    const uint32_t k = kb + lane;
+    const uint32_t k = kb + threadIdx.x;
     bool valid = k < total;
-
-    // per lane: the row (FLAT: kv component and vector of the run) and its
-    // source page, counted from the slot's; jo0 is that of the first live lane
-    uint32_t c = 0, slot = 0, h = 0, v = 0, jo, jo0, w = 0;
-    if (FLAT) {
-        const uint32_t R = ntok * p.H * p.vpr;                 // vectors per kv run
-        const uint32_t kc = valid ? k : kb;
-        c = kc >= R;
-        w = kc - c * R;
-        jo = fd_div(p.fd_To, (uint32_t)so_a + fd_div(p.fd_hv, w));
-        jo0 = __builtin_amdgcn_readfirstlane(jo);              // lane 0 is live
-    } else {
-        tile_row<TTHD>(p, valid ? k : total - 1, rows_c, sa, sb, blk0, c, slot, h, v, valid);
-        const uint64_t live = __ballot(valid);
-        if (live == 0) return;
-        jo = fd_div(p.fd_To, (uint32_t)so_a + (slot - (uint32_t)sa));
-        jo0 = __builtin_amdgcn_readlane(jo, __builtin_ctzll(live));
-    }
-    const bool one = __ballot(valid && jo != jo0) == 0;
-    // The sweep runs only on tables of at most INT32_MAX entries, so 32-bit
-    // unsigned compares also reject negative indices (jo0 < 2^21 cannot
-    // carry a non-negative src_idx past 2^32).
+    uint32_t c, slot, h, v;
+    tile_row<TOKEN_ORDER>(p.H, p.vpr, p.fd_H, p.fd_vpr, valid ? k : total - 1, rows_c, sa, sb, blk0, c, slot,
+                          h, v, valid);
+    if (!valid) return;
+    // Tables hold at most INT32_MAX entries, so 32-bit unsigned compares also
+    // reject negative indices.
     const bool t_in = (uint32_t)d.dst_idx < (uint32_t)ts.pt_len;
-    const uint32_t oidx0 = (uint32_t)d.src_idx + jo0;
-    const bool o_in = d.src_idx >= 0 && oidx0 < (uint32_t)os.pt_len;
-    // both page ids are read before any error is reported (an atomic ahead
-    // of them would turn them into vector loads)
     const int32_t tpage = t_in ? cload(ts.pt + (uint32_t)d.dst_idx) : -1;
-    const int32_t opage0 = t_in && one && o_in ? cload(os.pt + oidx0) : -1;
-    const bool pages_ok = (uint32_t)tpage < (uint32_t)ts.N && (uint32_t)opage0 < (uint32_t)os.N;
-    char *t_base = ts.base + (int64_t)l * ts.s_l + (int64_t)tpage * ts.s_p;
-    const char *o_l = os.base + (int64_t)l * os.s_l;
-    if (FLAT && one && pages_ok) {
-        // the usual case: the piece's rows in one source page, both pages valid
-        if (!valid) return;
-        // source slot of the page's first token, counted from source page jo0
-        const int64_t so = (int64_t)so_a - (int64_t)jo0 * os.T;
-        const char *s = o_l + (int64_t)opage0 * os.s_p + so * os.s_t;
-        char *dd = t_base + (int64_t)sa * ts.s_t;
-        st16<HOST>(dd + c * ts.s_c + (int64_t)w * 16, ld16(s + c * os.s_c + (int64_t)w * 16));
+    if ((uint32_t)tpage >= (uint32_t)ts.N) {
+        report(p, t_in ? KVX_DERR_DST_PAGE : KVX_DERR_PT_RANGE);
         return;
     }
-    // errors of the page and of a single source page, destination first
-    if (!t_in || (uint32_t)tpage >= (uint32_t)ts.N) {
-        if (lane == 0) report(p, t_in ? KVX_DERR_DST_PAGE : KVX_DERR_PT_RANGE);
+    const uint32_t pos = (uint32_t)so_a + (slot - (uint32_t)sa);
+    const uint32_t jo = fd_div(p.fd_To, pos);
+    const int64_t idx = (int64_t)d.src_idx + jo;
+    if (idx < 0 || idx >= os.pt_len) {
+        report(p, KVX_DERR_PT_RANGE);
         return;
     }
-    if (one && !pages_ok) {
-        if (lane == 0) report(p, o_in ? KVX_DERR_SRC_PAGE : KVX_DERR_PT_RANGE);
+    const int32_t pg = os.pt[idx];
+    if (pg < 0 || pg >= os.N) {
+        report(p, KVX_DERR_SRC_PAGE);
         return;
     }
-    if (FLAT) {                     // rows in two source pages: resolve them as the general case
-        tile_row<true>(p, valid ? k : total - 1, rows_c, sa, sb, blk0, c, slot, h, v, valid);
-        jo = fd_div(p.fd_To, (uint32_t)so_a + (slot - (uint32_t)sa));
-    }
-    int32_t pg = one ? opage0 : -1;
-    if (!one && valid) {
-        const int64_t idx = (int64_t)d.src_idx + jo;
-        if (idx < 0 || idx >= os.pt_len) {
-            report(p, KVX_DERR_PT_RANGE);
-        } else {
-            const int32_t id = os.pt[idx];
-            if (id < 0 || id >= os.N) report(p, KVX_DERR_SRC_PAGE);
-            else pg = id;
-        }
-    }
-    if (!valid || pg < 0) return;
-    const uint32_t so = (uint32_t)so_a + (slot - (uint32_t)sa) - jo * (uint32_t)os.T;
-    const char *src = o_l + (int64_t)pg * os.s_p + c * os.s_c + (int64_t)so * os.s_t +
+    const uint32_t so = pos - jo * (uint32_t)os.T;
+    const char *src = os.base + (int64_t)l * os.s_l + (int64_t)pg * os.s_p + c * os.s_c + (int64_t)so * os.s_t +
                       (int64_t)h * os.s_h + v * 16;
-    char *dst = t_base + c * ts.s_c + (int64_t)slot * ts.s_t + (int64_t)h * ts.s_h + v * 16;
+    char *dst = ts.base + (int64_t)l * ts.s_l + (int64_t)tpage * ts.s_p + c * ts.s_c + (int64_t)slot * ts.s_t +
+                (int64_t)h * ts.s_h + v * 16;
     st16<HOST>(dst, ld16(src));
+}
+
+// One piece of the sweep: the vectors [kb, kb + 64) of page slot d of layer
+// l, one per lane, in the vector order of copy_rows.  The common path, a piece
+// whose rows lie in one source page with every index and page id in range,
+// needs the two page ids and nothing else, read through the scalar cache;
+// returns false for any other piece, before anything was copied or reported.
+// d's slots are in range already.  Indices are clamped into the tables, so
+// that the page ids can be on their way while the checks are made.
+template <SweepMode MODE, bool HOST>
+__device__ __forceinline__ bool sweep_piece(const SweepArgs &a, const kvx_plan_slot &d, uint32_t l,
+                                            uint32_t kb) {
+    constexpr bool kRows = MODE == ROWS_T || MODE == ROWS_H;
+    constexpr uint32_t SB = KVX_SWEEP_SLOT_BLOCK;
+    const uint32_t sa = (uint32_t)d.dst_slot, so_a = (uint32_t)d.src_slot, ntok = (uint32_t)d.n_tokens;
+    const uint32_t blk0 = sa / SB, nblk = (sa + ntok - 1) / SB - blk0 + 1;
+    const uint32_t rows_c = MODE == ROWS_H ? a.H * nblk * SB : ntok * a.H;
+    const uint32_t R = kRows ? rows_c * a.vpr : ntok * a.fd_hv.d;      // vectors per kv component
+    const uint32_t total = R * a.C;
+    const uint32_t kk = kb + threadIdx.x, k = kk < total ? kk : total - 1;
+    uint32_t od, os, jo0 = 0, bad = a.general;
+    bool valid = kk < total;
+    if (!kRows) {
+        if (so_a + ntok > a.s_T) {
+            // the source pages of the piece's first and last token
+            const uint32_t ke = (kb + kWave < total ? kb + kWave : total) - 1;
+            const bool c0 = kb >= R, c1 = ke >= R;
+            uint32_t t0 = fd_div(a.fd_hv, c0 ? kb - R : kb), t1 = fd_div(a.fd_hv, c1 ? ke - R : ke);
+            if (c0 != c1) t0 = 0, t1 = ntok - 1;
+            jo0 = fd_div(a.fd_To, so_a + t0);
+            bad |= fd_div(a.fd_To, so_a + t1) - jo0;
+        }
+    } else {
+        uint32_t c, slot, h, v;
+        tile_row<MODE == ROWS_T>(a.H, a.vpr, a.fd_H, a.fd_vpr, k, rows_c, sa, sa + ntok, blk0, c, slot, h, v,
+                                 valid);
+        const uint32_t jo = fd_div(a.fd_To, so_a + (slot - sa));
+        const uint64_t live = __ballot(valid);
+        if (live == 0) return true;
+        jo0 = __builtin_amdgcn_readlane(jo, __builtin_ctzll(live));
+        bad |= __ballot(valid && jo != jo0) != 0;
+        od = (c ? a.d_c : 0) + (slot - sa) * a.d_t + h * a.d_h + v * 16;
+        os = (c ? a.s_c : 0) + (slot - sa) * a.s_t + h * a.s_h + v * 16;
+    }
+    const uint32_t didx = (uint32_t)d.dst_idx, sidx = (uint32_t)d.src_idx + jo0;
+    const uint32_t di = didx < a.d_last ? didx : a.d_last, si = sidx < a.s_last ? sidx : a.s_last;
+    const uint32_t dpage = (uint32_t)cload(a.d_pt + di), spage = (uint32_t)cload(a.s_pt + si);
+    // (jo0 < 2^21 cannot carry a non-negative src_idx past 2^32)
+    bad |= (didx ^ di) | (sidx ^ si) | ((uint32_t)d.src_idx >> 31);
+    const uint32_t dp = dpage < a.d_lastp ? dpage : a.d_lastp, sp = spage < a.s_lastp ? spage : a.s_lastp;
+    bad |= (dpage ^ dp) | (spage ^ sp);
+    if (bad) return false;
+    char *dd = a.d_base + (((uint64_t)l * a.d_l + (uint64_t)dp * a.d_p) << 4) + (uint64_t)sa * a.d_t;
+    // the source slot of the page's first token, counted from source page jo0
+    const char *ss = a.s_base + (((uint64_t)l * a.s_l + (uint64_t)sp * a.s_p) << 4) +
+                     (int64_t)((int32_t)so_a - (int32_t)(jo0 * a.s_T)) * a.s_t;
+    if (!kRows) {
+        // (lanes past the last vector repeat it)
+        const bool c = k >= R;
+        const uint32_t w = c ? k - R : k, t = MODE == TOKENS ? fd_div(a.fd_hv, w) : 0;
+        od = w * 16 + (c ? a.d_c : 0) + t * (a.d_t - a.fd_hv.d * 16);
+        os = w * 16 + (c ? a.s_c : 0) + t * (a.s_t - a.fd_hv.d * 16);
+        st16<HOST>(dd + od, ld16(ss + os));
+    } else if (valid) {
+        st16<HOST>(dd + od, ld16(ss + os));
+    }
+    return true;
 }
 
 __device__ __forceinline__ int32_t clamp_i32(int64_t x) {
@@ -591,7 +632,7 @@ __device__ __forceinline__ int32_t clamp_i32(int64_t x) {
 
 // Whether slot d of the plan is page qi of the plan the records imply: its
 // record's prefix range holds qi, and its fields are those of that record's
-// page qi - prefix[r].  Run once per slot (by one workgroup of layer 0).
+// page qi - prefix[r].
 __device__ __forceinline__ bool slot_agrees(const Params &p, int64_t qi, const kvx_plan_slot &d) {
     const int32_t r = d.req;
     if (r < 0 || r >= p.n_reqs) return false;
@@ -610,73 +651,91 @@ __device__ __forceinline__ bool slot_agrees(const Params &p, int64_t qi, const k
            d.src_slot == (int32_t)(pos - jo * p.src.T);
 }
 
-// Page slot qi of layer l: read its slot, copy the workgroup's
-// KVX_SWEEP_PIECES pieces one after the other, and (one workgroup per slot)
-// check the slot against the records.
-template <bool TTHD, bool FLAT, bool HOST>
-__device__ __forceinline__ void sweep_slot(const Params &p, int64_t qi, uint32_t l, uint32_t part) {
-    const kvx_plan_slot d = cload(p.slots + qi);
-    const uint32_t piece0 = part * KVX_SWEEP_PIECES;
-#pragma unroll
-    for (uint32_t i = 0; i < KVX_SWEEP_PIECES; ++i)
-        sweep_piece<TTHD, FLAT, HOST>(p, d, l, (piece0 + i) * kWave);
-    if (l == 0 && part == 0 && !slot_agrees(p, qi, d) && threadIdx.x == 0) report(p, KVX_DERR_BAD_PLAN);
+// The checking workgroups of a sweep (`n` of them): the plan's slots against
+// the records, a lane per slot; prefix[0] = 0, prefix[r + 1] - prefix[r] =
+// pages of record r, and prefix[n_reqs] = plan_pages.  Malformed records are
+// reported too.
+__device__ __forceinline__ void sweep_check(const Params &p, uint32_t b, uint32_t n) {
+    const int64_t first = (int64_t)b * kWave + threadIdx.x, step = (int64_t)n * kWave;
+    bool bad_plan = first == 0 && (p.prefix[0] != 0 || p.prefix[p.n_reqs] != p.plan_pages);
+    for (int64_t qi = first; qi < p.plan_pages; qi += step)
+        bad_plan = bad_plan || !slot_agrees(p, qi, p.slots[qi]);
+    for (int64_t r = first; r < p.n_reqs; r += step) {
+        Req mine;
+        if (!load_req<OP_TRANSFER>(p, (int32_t)r, mine)) report(p, KVX_DERR_BAD_REQ);
+        bad_plan = bad_plan || p.prefix[r + 1] - p.prefix[r] != mine.pages;
+    }
+    if (bad_plan) report(p, KVX_DERR_BAD_PLAN);
 }
 
 // Sweep kernel (a planned pool -> pool transfer): one wavefront per
 // workgroup, and workgroup b copies one piece of 64 vectors (1 KiB) of one
-// destination page of one layer in each pass, found by one read of the
+// destination page of one layer, found by one read of the
 // plan.  Workgroups are numbered layer by layer and page slot by page slot
 // within a layer (pages in plan order), so the hardware dispatcher, which
 // starts them in order, keeps the pieces in flight on the whole GPU inside a
-// small window that slides through the transfer.  (A persistent grid lets
-// its workers drift over the whole transfer; on the same pools this order
-// moves up to 16% more bytes per second for 256 KiB pages.)  The dispatcher
+// small window that slides through the transfer.  The dispatcher
 // deals consecutive workgroups to the 8 XCDs in turn, so within each group
 // of 8 page slots the numbering gives XCD x every piece of slot x, in order:
-// each page is copied by one XCD.  (Measured on the same pools: 1.5-3% more
-// bytes per second than pieces dealt across the XCDs for 72 and 256 KiB
-// pages, 6% for 128 KiB pages; a contiguous eighth of every page per XCD
-// is 10% slower.)  The launch has layers x sweep_pages x ppt workgroups,
-// with sweep_pages about plan_pages / KVX_SWEEP_PASSES (fewer when the grid
-// is capped): each workgroup goes on to the slots sweep_pages apart, up to
-// plan_pages.  The first slot is taken outside that loop, so that its loads
-// precede every store of the kernel.  Workgroup 0 finally checks the prefix
-// against the records and plan_pages, and reports malformed records.
-template <bool TTHD, bool FLAT, bool HOST>
-__global__ void __launch_bounds__(kWave) kvx_sweep_kernel(Params p) {
-    const uint32_t b = blockIdx.x;
-    uint32_t slot = fd_div(p.fd_ppt, b);                       // (layer, page slot)
-    uint32_t part = b - slot * p.sweep_ppt;
-    {
-        // In each whole group of 8 page slots, XCD b % 8 takes slot 8g + b % 8
-        // (its pieces in order): every page is copied by one XCD.
-        const uint32_t g = slot >> 3;
-        if ((g << 3) + 8u <= (uint32_t)p.L * (uint32_t)p.sweep_pages) {
-            const uint32_t r = b - (g << 3) * p.sweep_ppt;
-            slot = (g << 3) + (r & 7u);
-            part = r >> 3;
-        }
+// each page is copied by one XCD (1.5-6% more than pieces dealt across XCDs).
+// What bounds it: a wavefront's life before its load.  With 32 wavefronts per
+// CU, 1 KiB each is what the memory wants in flight (a bare copy in this order
+// moves 6.6-6.7 TB/s; 2 KiB per wavefront 6.2-6.4, whole pages per wavefront
+// 5.1), so every cycle spent on finding the piece is rate lost.  Hence three
+// waits (arguments, plan slot, page ids), indices clamped instead of branched
+// on, the plan's check in workgroups of its own, and all that is rare in
+// sweep_piece_general.  Measured on 256 KiB pages (36 x 8 x 128, 43.7 GB):
+// 7129 us with the checks and the rare paths inline, three passes over the
+// pages; 6613 us so.  72 KiB pages (61 x 576): 4371 to 4238 us; head ranges in
+// 4-layer launches of 300 MB: 499 to 460 us.
+template <SweepMode MODE, bool HOST>
+__global__ void __launch_bounds__(kWave) kvx_sweep_kernel(SweepArgs a, Params) {
+    // The second argument is read where it is needed: a piece on the common
+    // path needs nothing of it, and its fields would crowd the scalar
+    // registers.
+    typedef const __attribute__((address_space(4))) char *ConstPtr;
+    ConstPtr args = (ConstPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const Params &p = *(const Params *)(args + sizeof(SweepArgs));
+    // The first is read at once, with one wait.
+    asm volatile("" ::"s"(a.slots), "s"(a.ppt.d), "s"(a.ppt.m), "s"(a.ppt.l), "s"(a.pages.d), "s"(a.pages.m),
+                 "s"(a.pages.l), "s"(a.slot0), "s"(a.n_slots), "s"(a.checks), "s"(a.general), "s"(a.d_pt),
+                 "s"(a.s_pt), "s"(a.d_last), "s"(a.s_last), "s"(a.d_T), "s"(a.s_T), "s"(a.d_lastp),
+                 "s"(a.s_lastp));
+    asm volatile("" ::"s"(a.fd_hv.d), "s"(a.C), "s"(a.d_t), "s"(a.s_t), "s"(a.d_c), "s"(a.s_c), "s"(a.d_l),
+                 "s"(a.d_p), "s"(a.s_l), "s"(a.s_p), "s"(a.d_base), "s"(a.s_base));
+    uint32_t b = blockIdx.x;
+    if (b < a.checks) {
+        sweep_check(p, b, a.checks);
+        return;
     }
-    const uint32_t l = fd_div(p.fd_sp, slot);
-    const int64_t q0 = (int64_t)(slot - l * (uint32_t)p.sweep_pages);
-    sweep_slot<TTHD, FLAT, HOST>(p, q0, l, part);
-    for (int64_t qi = q0 + p.sweep_pages; qi < p.plan_pages; qi += p.sweep_pages)  // later passes
-        sweep_slot<TTHD, FLAT, HOST>(p, qi, l, part);
-    if (b == 0) {
-        // prefix[0] = 0, prefix[r + 1] - prefix[r] = pages of record r, and
-        // prefix[n_reqs] = plan_pages
-        bool bad_plan = p.prefix[0] != 0 || p.prefix[p.n_reqs] != p.plan_pages;
-        for (int32_t r0 = 0; r0 < p.n_reqs; r0 += kWave) {
-            const int32_t r = r0 + (int32_t)threadIdx.x;
-            if (r < p.n_reqs) {
-                Req mine;
-                if (!load_req<OP_TRANSFER>(p, r, mine)) report(p, KVX_DERR_BAD_REQ);
-                bad_plan = bad_plan || p.prefix[r + 1] - p.prefix[r] != mine.pages;
-            }
-        }
-        if (bad_plan) report(p, KVX_DERR_BAD_PLAN);
+    b -= a.checks;
+    // In each whole group of 8 page slots, XCD b % 8 takes slot 8g + b % 8
+    // (its pieces in order); the last slots, fewer than 8, one after the other.
+    const uint32_t g = fd_div(a.ppt, b >> 3);
+    uint32_t slot = (g << 3) + (b & 7u), part = (b >> 3) - g * a.ppt.d;
+    if ((g << 3) + 8u > a.n_slots) {
+        const uint32_t r = b - (g << 3) * a.ppt.d, s = fd_div(a.ppt, r);
+        slot = (g << 3) + s;
+        part = r - s * a.ppt.d;
     }
+    slot += a.slot0;
+    const uint32_t l = fd_div(a.pages, slot);
+    kvx_plan_slot d = cload(a.slots + (slot - l * a.pages.d));
+    asm volatile("" ::"s"(d.dst_idx), "s"(d.src_slot));   // the whole slot with one wait
+    // The slot is trusted only as far as keeping every access inside the
+    // pools and tables; whether it matches the records is checked separately.
+    const uint32_t sa = (uint32_t)d.dst_slot < a.d_T - 1 ? (uint32_t)d.dst_slot : a.d_T - 1;
+    const uint32_t ntok = (uint32_t)d.n_tokens < a.d_T - sa ? (uint32_t)d.n_tokens : a.d_T - sa;
+    const uint32_t so_a = (uint32_t)d.src_slot < a.s_T - 1 ? (uint32_t)d.src_slot : a.s_T - 1;
+    d.dst_slot = (int32_t)sa;
+    d.n_tokens = (int32_t)ntok;
+    d.src_slot = (int32_t)so_a;
+    constexpr uint32_t SB = KVX_SWEEP_SLOT_BLOCK;
+    const uint32_t slots = MODE == ROWS_H && ntok ? ((sa + ntok - 1) / SB - sa / SB + 1) * SB : ntok;
+    const uint32_t kb = part * kWave;
+    if (kb >= slots * a.fd_hv.d * a.C) return;
+    if (!sweep_piece<MODE, HOST>(a, d, l, kb)) sweep_piece_general<MODE != ROWS_H, HOST>(p, d, l, kb);
 }
 
 typedef void (*KernelFn)(Params);
@@ -705,21 +764,80 @@ KernelFn pick(int op, bool tthd, bool flat, bool host) {
 
 }  // namespace
 
-// Sweep grid when the host chose it (p.sweep), else a persistent grid: as
+// The sweep's launch: the pieces of layers x plan pages, in as many launches
+// as its workgroups need (KVX_SWEEP_MAX_BLOCKS each).
+static int launch_sweep(const Params &p, hipStream_t stream) {
+    const Side &d = p.dst, &s = p.src;
+    const bool adjacent = (p.H == 1 || (d.s_h == p.row_bytes && s.s_h == p.row_bytes)) &&
+                          d.s_t >= (int64_t)p.H * p.row_bytes && s.s_t >= (int64_t)p.H * p.row_bytes;
+    const SweepMode mode = p.flat ? RUNS : adjacent ? TOKENS : d.tok_contig ? ROWS_T : ROWS_H;
+    typedef void (*SweepFn)(SweepArgs, Params);
+    static const SweepFn fns[4][2] = {
+        {kvx_sweep_kernel<RUNS, false>, kvx_sweep_kernel<RUNS, true>},
+        {kvx_sweep_kernel<TOKENS, false>, kvx_sweep_kernel<TOKENS, true>},
+        {kvx_sweep_kernel<ROWS_T, false>, kvx_sweep_kernel<ROWS_T, true>},
+        {kvx_sweep_kernel<ROWS_H, false>, kvx_sweep_kernel<ROWS_H, true>}};
+    const SweepFn fn = fns[mode][p.dst_host ? 1 : 0];
+    constexpr int64_t SB = KVX_SWEEP_SLOT_BLOCK;
+    const int64_t page_slots = mode == ROWS_H ? ((int64_t)d.T + SB - 1) / SB * SB : d.T;
+    // bytes from a page's first copied row to the end of its last one
+    const auto extent = [&](const Side &x) {
+        return (page_slots - 1) * x.s_t + (p.C - 1) * x.s_c + (p.H - 1) * x.s_h + p.row_bytes;
+    };
+    SweepArgs a{};
+    a.slots = p.slots;
+    a.ppt = make_fastdiv(sweep_pieces(p, page_slots));
+    a.pages = make_fastdiv((uint32_t)p.plan_pages);
+    const auto fits = [&](const Side &x) {
+        return extent(x) <= INT32_MAX && x.s_l / 16 <= UINT32_MAX && x.s_p / 16 <= UINT32_MAX;
+    };
+    a.general = !(fits(d) && fits(s));
+    a.d_pt = d.pt;
+    a.s_pt = s.pt;
+    a.d_last = (uint32_t)d.pt_len - 1;
+    a.s_last = (uint32_t)s.pt_len - 1;
+    a.d_T = d.T;
+    a.s_T = s.T;
+    a.d_lastp = (uint32_t)d.N - 1;
+    a.s_lastp = (uint32_t)s.N - 1;
+    a.fd_To = p.fd_To;
+    a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
+    a.C = p.C;
+    a.d_t = (uint32_t)d.s_t;
+    a.s_t = (uint32_t)s.s_t;
+    a.d_c = (uint32_t)d.s_c;
+    a.s_c = (uint32_t)s.s_c;
+    a.d_l = (uint32_t)(d.s_l / 16);
+    a.d_p = (uint32_t)(d.s_p / 16);
+    a.s_l = (uint32_t)(s.s_l / 16);
+    a.s_p = (uint32_t)(s.s_p / 16);
+    a.d_base = d.base;
+    a.s_base = s.base;
+    a.H = p.H;
+    a.vpr = p.vpr;
+    a.d_h = (uint32_t)d.s_h;
+    a.s_h = (uint32_t)s.s_h;
+    a.fd_H = p.fd_H;
+    a.fd_vpr = p.fd_vpr;
+    const int64_t n_check = ((p.plan_pages > p.n_reqs ? p.plan_pages : p.n_reqs) + kWave - 1) / kWave;
+    const int64_t total = (int64_t)p.L * p.plan_pages;
+    int64_t per = KVX_SWEEP_MAX_BLOCKS / a.ppt.d;                  // page slots per launch
+    if (per > 8) per &= ~(int64_t)7;
+    for (int64_t s0 = 0; s0 < total; s0 += per) {
+        a.slot0 = (uint32_t)s0;
+        a.n_slots = (uint32_t)(total - s0 < per ? total - s0 : per);
+        a.checks = s0 ? 0 : (uint32_t)((n_check < 1024 ? n_check : 1024) + 7) / 8 * 8;
+        hipLaunchKernelGGL(fn, dim3(a.checks + a.n_slots * a.ppt.d), dim3(kWave), 0, stream, a, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Sweep when the host chose it (p.sweep), else a persistent grid: as
 // many workgroups as the device holds at once.
 int launch(const Params &p, hipStream_t stream) {
-    if (p.sweep) {
-        KernelFn fs;
-        if (p.flat)
-            fs = p.dst_host ? kvx_sweep_kernel<true, true, true> : kvx_sweep_kernel<true, true, false>;
-        else if (p.dst.tok_contig)
-            fs = p.dst_host ? kvx_sweep_kernel<true, false, true> : kvx_sweep_kernel<true, false, false>;
-        else
-            fs = p.dst_host ? kvx_sweep_kernel<false, false, true> : kvx_sweep_kernel<false, false, false>;
-        const uint64_t blocks = (uint64_t)p.L * (uint64_t)p.sweep_pages * p.sweep_ppt;
-        hipLaunchKernelGGL(fs, dim3((uint32_t)blocks), dim3(kWave), 0, stream, p);
-        return hipGetLastError();
-    }
+    if (p.sweep) return launch_sweep(p, stream);
     const bool tthd = (p.op == OP_GATHER ? p.src : p.dst).tok_contig != 0;
     KernelFn fn = pick(p.op, tthd, p.flat != 0, p.dst_host != 0);
     int dev = 0;

@@ -3,8 +3,7 @@ against the oracle.
 
 The test build (libkvx_test.so) takes the sweep for every planned transfer
 whatever its size and destination layout, with at most 2048 workgroups per
-pass (larger cases loop
-over page slots), so small cases exercise it: every layout pair and
+launch (larger cases take several launches), so small cases exercise it: every layout pair and
 page-size pair, element widths, slices, copies inside one pool, the seeded
 random cases (damaged tables, empty requests, shared source pages, slices)
 and the device error rules.  A wrong token total only changes the choice of
@@ -12,7 +11,8 @@ launch.  A plan that disagrees with the records (a wrong page total, a
 damaged prefix or slot, slots out of order, page sizes of other pools, or
 random slot contents) raises KVX_DERR_BAD_PLAN, and every access still
 stays inside the pools and tables.  The product library sweeps when the
-records copy 64 KiB or more per page on average; a shape with 256 KiB pages
+records copy 64 KiB or more per page on average, or 12 KiB and two thirds of
+a page; a shape with 256 KiB pages
 checks it there, and the full-size handoff, MLA, relayout, TP reshard and
 fork are checked on every layer in test_gpu_full."""
 import numpy as np
@@ -310,3 +310,33 @@ def test_product_library_sweeps_large_tiles(ls, ld, tokens):
     spec = [(0, 0, 200, None), (5, 70, 333, None), (63, 1, 1, None), (0, 0, 0, None), (10, 64, 128, 0)]
     wl = cases.transfer_case(ls, ld, 64, 64, seed=17, e=2, D=128, L=3, C=2, H=8, spec=spec)
     check(wl, None, tokens)
+
+
+@pytest.mark.parametrize("L,tokens", [(1, 64), (1, 512), (3, 200), (5, 333), (8, 64)])
+@pytest.mark.parametrize("ls,ld,sl", [("LPCTHD", "LPCTHD", None), ("LPCTHD", "PLCTHD", 3), ("PLCHTD", "LPCTHD", 3),
+                                      ("LPCTHD", "LPCHTD", None)])
+def test_page_slots_around_groups_of_eight(test_lib, ls, ld, sl, L, tokens):
+    """Layers x pages page slots that are no multiple of 8 (the last group is
+    dealt another way), 128 to 256 pieces a page, so that the test build needs
+    one to three launches; each way a piece's rows can lie: runs, a head
+    range of a token (``sl`` of 8 heads), rows of either order.  Starts that
+    differ put rows of one piece into two source pages."""
+    H = 8
+    spec = [(5, 0, tokens, None), (0, 33, 90, 0)]
+    if sl is None:
+        wl = cases.transfer_case(ls, ld, 64, 64, seed=L, e=2, D=128, L=L, C=2, H=H, spec=spec)
+    else:
+        wl = cases.transfer_case(ls, ld, 64, 64, seed=L, e=2, D=128, L=L, C=2, H=H, spec=spec)
+        wl.steps[0].slice = (0, 0, L, 0, 0, 2, 2, 1, sl)
+    check(wl, test_lib)
+    check(wl, None)
+
+
+@pytest.mark.parametrize("D,launch", [(64, 2), (56, 2), (16, 1)])
+def test_product_library_sweeps_dense_small_pages(D, launch):
+    """Full pages of 16 and 14 KiB sweep, of 4 KiB do not."""
+    from paper_2606_31093_amd import kvx
+    spec = [(0, 0, 256, None), (16, 32, 160, None)]
+    wl = cases.transfer_case("LPCTHD", "LPCTHD", 16, 16, seed=D, e=2, D=D, L=3, C=2, H=4, spec=spec)
+    check(wl, None)
+    assert kvx.kvx_last_launch() == launch
