@@ -253,7 +253,7 @@ int check_common(const kvx_req *reqs, int32_t n_reqs, uint32_t *dev_err) {
 // Device views of every pointer a launch uses.
 struct Views {
     void *src = nullptr, *dst = nullptr;
-    bool dst_host = false;
+    bool src_host = false, dst_host = false;
     const int32_t *src_pt = nullptr, *dst_pt = nullptr;
     const kvx_req *reqs = nullptr;
     uint32_t *err = nullptr;
@@ -265,7 +265,7 @@ int view_all(const void *src, int64_t src_bytes, const void *dst, int64_t dst_by
     int st;
     void *d = nullptr;
     // A NULL base here is an empty buffer (pools are never NULL): nothing to view.
-    if (src && (st = device_view(src, src_bytes, "src base", &v.src))) return st;
+    if (src && (st = device_view(src, src_bytes, "src base", &v.src, &v.src_host))) return st;
     if (dst && (st = device_view(dst, dst_bytes, "dst base", &v.dst, &v.dst_host))) return st;
     if (src_pt_len > 0) {
         if ((st = device_view(src_pt, src_pt_len * 4, "src_pt", &d))) return st;
@@ -298,6 +298,7 @@ void finish_params(kvx::Params &P, const Shape &s, const Views &v, int32_t n_req
     P.vpr = P.row_bytes / 16;
     P.elem_bytes = s.e;
     P.flat = P.src.tok_contig && P.dst.tok_contig;
+    P.src_host = v.src_host;
     P.dst_host = v.dst_host;
     const kvx::Side &os = P.op == kvx::OP_GATHER ? P.dst : P.src;
     P.fd_vpr = kvx::make_fastdiv((uint32_t)P.vpr);

@@ -95,8 +95,8 @@ struct Params {
     int32_t row_bytes;   // head_dim * elem_bytes, a multiple of 16
     int32_t vpr;         // 16-byte vectors per row
     int32_t elem_bytes;
-    int32_t flat;        // both sides tok_contig: a tile is C contiguous runs per piece
-    int32_t dst_host;    // the destination is pinned host memory (plain stores)
+    int32_t flat;        // both sides tok_contig: a page is C contiguous runs on both
+    int32_t src_host, dst_host;   // the side is pinned host memory
     FastDiv fd_vpr, fd_H, fd_To;
     FastDiv fd_Tt;       // tiling side's page_tokens
     // Sweep launch (a planned pool -> pool transfer): prefix[r] =

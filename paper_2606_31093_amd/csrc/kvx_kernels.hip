@@ -1,39 +1,35 @@
 // kvx_kernels.hip -- the copy engine of libkvx: HIP kernels for gfx950.
 //
-// One kernel moves the rows named by a batch of request records from a
+// They move the rows named by a batch of request records from a
 // source side to a destination side (Omni-Flow Sec. 4.1.1: layer x page x
 // slice addressing; Sec. 4.1.2: conversion between the paged layout and the
 // flat serialization; Sec. 5.2: slot -> page translation through a table).
 // Nothing is computed on the data: every element moves as raw bytes inside
-// 16-byte vectors, so the kernel is bound by HBM (or the host link when a
+// 16-byte vectors, so the kernels are bound by HBM (or the host link when a
 // side is pinned host memory).
 //
-// Work decomposition.  A tile is (request r, page j of the tiling side,
-// layer l); the tiling side is the destination pool for transfer and
-// scatter (each tile then writes one destination page of one layer, and no
-// two tiles write the same bytes) and the source pool for gather.  A
-// persistent grid of workgroups strides over the flat tile index.  Each
-// workgroup reads the request records 256 at a time, one per thread, turns
-// their tile counts into tile ranges with a scan in LDS and finds the record
-// of each of its tiles by binary search, so no tile table or scratch memory
-// is needed and thousands of small requests cost a few parallel loads per
-// chunk rather than a chain of dependent ones.  A tile is copied by one
-// worker: a wavefront when the launch copies contiguous runs (four small
-// tiles in flight per workgroup), the whole workgroup when it resolves rows.
+// The unit of work is one page of the tiling side in one layer; the tiling
+// side is the destination pool for transfer and
+// scatter (each unit then writes one destination page of one layer, and no
+// two units write the same bytes) and the source pool for gather.  Four
+// kernels share the work out:
+// - kvx_sweep_kernel: a planned transfer, one workgroup of one wavefront per
+//   kilobyte of a unit, started in order by the hardware;
+// - kvx_order_kernel: unplanned calls of long records whose tokens are runs
+//   on both sides, a persistent grid that keeps that order;
+// - kvx_parts_kernel: the other unplanned calls of runs (few or short
+//   records, the host link), a persistent grid over parts of units;
+// - kvx_copy_kernel: unplanned calls that resolve rows (a head-major side), a
+//   persistent grid over whole units.
 //
-// Inside a tile the tiling side's rows are a fixed page of one layer.  The
-// other side's rows come from one or more of its pages ("pieces"), whose ids
-// each wavefront loads once into lanes 0..K-1 and broadcasts with a lane
-// shuffle.  When both sides keep the rows of consecutive tokens adjacent
-// (token-major layouts and the flat buffer) and the tile maps onto a single
-// piece, a tile is C contiguous runs on both sides and the copy is a plain
-// vector stream; otherwise each 16-byte vector resolves its row.
+// Order matters because of the memory, not of the caches: nothing is re-read.
+// A bare copy of random 256 KiB pages moves 6.6 TB/s (read + write) when the
+// kilobytes in flight all lie in a few pages being walked through, and 5.1 to
+// 6.3 TB/s, depending on where the pools sit in physical memory, when every
+// wavefront walks through a page of its own.
 
 #include "kvx_internal.h"
 
-#ifndef KVX_UNROLL_FLAT
-#define KVX_UNROLL_FLAT 8
-#endif
 #ifndef KVX_UNROLL_ROWS
 #define KVX_UNROLL_ROWS 4
 #endif
@@ -49,29 +45,62 @@
 #ifndef KVX_ROWS_BLOCKS_PER_CU
 #define KVX_ROWS_BLOCKS_PER_CU 3  // grid of launches that resolve rows (measured best)
 #endif
-#ifndef KVX_BLOCKS_PER_CU
-#define KVX_BLOCKS_PER_CU 0  // 0: as many as fit
+// kvx_parts_kernel: workgroups of 256 threads per CU, and 16-byte vectors in
+// flight per lane.  64 decode records (1-4 tokens of 36 x 8 x 128): 7 x 4
+// 12.9 us, 4 x 4 15.0, 6 x 8 13.4, 8 x 2 16.0.
+#ifndef KVX_PARTS_BLOCKS_PER_CU
+#define KVX_PARTS_BLOCKS_PER_CU 7
 #endif
-#ifndef KVX_BLOCK
-#define KVX_BLOCK 256
+#ifndef KVX_PARTS_UNROLL
+#define KVX_PARTS_UNROLL 4
 #endif
-#ifndef KVX_FLAT_WAVE_TILES
-#define KVX_FLAT_WAVE_TILES 1  // launches of contiguous runs: one tile per wavefront
+// Parts per wavefront that units are cut into.  64 half-filled pages of 36
+// layers: 108 us with 32, 116 with 8.
+#ifndef KVX_GRID_PARTS
+#define KVX_GRID_PARTS 32
 #endif
-#ifndef KVX_ROWS_WAVE_TILES
-#define KVX_ROWS_WAVE_TILES 0  // launches that resolve rows: one tile per workgroup
+// The same over the host link: whole units, 8 vectors per lane (4: 1.8%
+// slower; units in parts 1.8%).
+#ifndef KVX_LINK_BLOCKS_PER_CU
+#define KVX_LINK_BLOCKS_PER_CU 5
+#endif
+#ifndef KVX_LINK_UNROLL
+#define KVX_LINK_UNROLL 8
+#endif
+// kvx_order_kernel: threads per workgroup, one workgroup per CU (256 KiB
+// pages, 43.7 GB: 7.0-7.35 ms; 512 threads, two workgroups, 7.05-7.2 ms, but
+// 72 KiB pages 5.1 against 4.75 ms and 288 KiB serializations 2.43 against
+// 2.28 ms).
+#ifndef KVX_ORDER_BLOCK
+#define KVX_ORDER_BLOCK 1024
+#endif
+// Which calls keep the order, judged on the device by the first 64 records:
+// full pages of at least KVX_ORDER_PIECES KiB, three quarters filled, and
+// KVX_ORDER_TURNS KiB to copy per wavefront.  Below them there is no order to
+// keep: 1-4 tokens of 64 records 18.3 us in order, 12.9 in parts; half-filled
+// pages 126 us in order, 108 in parts.  From 64 KiB pages up order wins
+// (64 KiB 1753 against 1925 us, 72 KiB 4751 against 4941, 256 KiB 7146
+// against 8591; on pools that happen to suit the grid 72 KiB pages lose 2%).
+#ifndef KVX_ORDER_PIECES
+#define KVX_ORDER_PIECES 40
+#endif
+#ifndef KVX_ORDER_QUARTERS
+#define KVX_ORDER_QUARTERS 3
+#endif
+#ifndef KVX_ORDER_TURNS
+#define KVX_ORDER_TURNS 16
+#endif
+// ... and, on the host, calls whose table holds this many entries per record:
+// one workgroup of 1024 threads per CU costs a small call 2-4 us.
+#ifndef KVX_ORDER_PAGES
+#define KVX_ORDER_PAGES 8
 #endif
 
 namespace kvx {
 namespace {
 
-constexpr int kBlock = KVX_BLOCK;
+constexpr int kBlock = 256;   // rows: the threads that copy a tile
 constexpr int kWave = 64;
-// A worker copies one tile at a time: a wavefront or the whole workgroup,
-// NT threads (a template parameter below).
-template <int NT>
-__device__ __forceinline__ uint32_t worker_tid() { return threadIdx.x % NT; }
-
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4u ld16(const char *p) {
@@ -168,35 +197,6 @@ __device__ __forceinline__ bool load_req(const Params &p, int32_t r, Req &q) {
     return true;
 }
 
-// Plain vector stream over C runs of R vectors each, by a worker of NT threads:
-// the vectors [kb, ke) of the tile in (c, vector) order.
-template <int NT, int U, bool HOST>
-__device__ __forceinline__ void copy_runs(char *d, const char *s, int64_t d_sc, int64_t s_sc,
-                                          uint32_t R, int32_t C, uint32_t kb, uint32_t ke) {
-    const uint32_t total = R * (uint32_t)C < ke ? R * (uint32_t)C : ke;
-    for (uint32_t k0 = kb + worker_tid<NT>(); k0 < total; k0 += NT * U) {
-        v4u v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t k = k0 + u * NT;
-            if (k < total) {
-                const uint32_t c = k >= R;
-                const uint32_t w = k - c * R;
-                v[u] = ld16(s + c * s_sc + (int64_t)w * 16);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t k = k0 + u * NT;
-            if (k < total) {
-                const uint32_t c = k >= R;
-                const uint32_t w = k - c * R;
-                st16<HOST>(d + c * d_sc + (int64_t)w * 16, v[u]);
-            }
-        }
-    }
-}
-
 // Everything a tile's row loop needs, fixed for the tile.
 struct Tile {
     const char *t_base;   // tiling side at (l, page, c = 0, slot = 0, h = 0)
@@ -216,9 +216,8 @@ struct Tile {
 // order when the tiling side is token-major (its memory order), else in
 // blocks of slots as described below, with the slots outside [sa, sb)
 // masked.
-template <int OP, bool TTHD, int NT, bool HOST, int U>
-__device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const Tile &t, uint32_t kb0,
-                                          uint32_t ke) {
+template <int OP, bool TTHD, bool HOST, int U>
+__device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const Tile &t) {
     constexpr bool kTileSrc = OP == OP_GATHER;
     constexpr bool kOtherBuf = OP != OP_TRANSFER;
     const Side &ts = kTileSrc ? p.src : p.dst;
@@ -233,17 +232,17 @@ __device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const T
     constexpr uint32_t SB = KVX_SLOT_BLOCK;
     const uint32_t blk0 = (uint32_t)t.sa / SB, nblk = ((uint32_t)t.sb - 1) / SB - blk0 + 1;
     const uint32_t rows_c = TTHD ? (uint32_t)t.ntok * H : H * nblk * SB;
-    const uint32_t total = rows_c * vpr * (uint32_t)p.C < ke ? rows_c * vpr * (uint32_t)p.C : ke;
+    const uint32_t total = rows_c * vpr * (uint32_t)p.C;
     const char *o_l = os.base + (int64_t)t.l * os.s_l;
     // The trip count is the same for every lane: the page-id broadcast below
     // reads other lanes, which must all still be active.
-    for (uint32_t kb = kb0; kb < total; kb += NT * U) {
+    for (uint32_t kb = 0; kb < total; kb += kBlock * U) {
         const char *src[U];
         char *dst[U];
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t kk = kb + worker_tid<NT>() + u * NT;
+            const uint32_t kk = kb + threadIdx.x + u * kBlock;
             const uint32_t k = kk < total ? kk : total - 1;
             bool valid = kk < total;
             const uint32_t rw = fd_div(p.fd_vpr, k);
@@ -304,11 +303,10 @@ __device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const T
     }
 }
 
-// Tile (request q, its tiling-side page jj, layer l): the vectors [kb, ke) of
-// the tile's vector order, U vectors per thread in flight.
-template <int OP, bool TTHD, int NT, bool HOST, int UF, int UR>
-__device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t jj, int32_t layer,
-                                        uint32_t kb, uint32_t ke) {
+// Tile (request q, its tiling-side page jj, layer l), U vectors per thread in
+// flight.
+template <int OP, bool TTHD, bool HOST, int U>
+__device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t jj, int32_t layer) {
     constexpr bool kTileSrc = OP == OP_GATHER;
     constexpr bool kOtherBuf = OP != OP_TRANSFER;
     const Side &ts = kTileSrc ? p.src : p.dst;
@@ -328,17 +326,16 @@ __device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t j
     // Tiling-side page (one per tile; a uniform load).
     const int64_t tidx = q.t_pt_off + j;
     if (tidx < 0 || tidx >= ts.pt_len) {
-        if (worker_tid<NT>() == 0) report(p, KVX_DERR_PT_RANGE);
+        if (threadIdx.x == 0) report(p, KVX_DERR_PT_RANGE);
         return;
     }
     const int32_t tpage = ts.pt[tidx];
     if (tpage < 0 || tpage >= ts.N) {
-        if (worker_tid<NT>() == 0) report(p, kTileSrc ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
+        if (threadIdx.x == 0) report(p, kTileSrc ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
         return;
     }
     t.t_base = ts.base + (int64_t)t.l * ts.s_l + (int64_t)tpage * ts.s_p;
 
-    const int64_t run_t = (int64_t)t.ntok * p.H * p.vpr;  // vectors per kv run
     if (kOtherBuf) {
         const int64_t H_row = (int64_t)p.H * p.row_bytes;
         const int64_t i0 = qa - q.t_start;
@@ -347,16 +344,6 @@ __device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t j
         t.pid = -1;
         t.qo_a = 0;
         t.jo0 = 0;
-        if (p.flat) {
-            const char *tb = t.t_base + (int64_t)t.sa * ts.s_t;
-            if (kTileSrc)
-                copy_runs<NT, UF, HOST>(const_cast<char *>(t.o_row0), tb, t.o_sc, ts.s_c,
-                                        (uint32_t)run_t, p.C, kb, ke);
-            else
-                copy_runs<NT, UF, HOST>(const_cast<char *>(tb), t.o_row0, ts.s_c, t.o_sc,
-                                        (uint32_t)run_t, p.C, kb, ke);
-            return;
-        }
     } else {
         const int32_t delta = q.o_start - q.t_start;
         t.qo_a = (int32_t)qa + delta;
@@ -375,21 +362,10 @@ __device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t j
                 if (id < 0 || id >= os.N) bad = KVX_DERR_SRC_PAGE;
                 else t.pid = id;
             }
-            if (bad && worker_tid<NT>() < kWave) report(p, bad);   // the worker's first wavefront
-        }
-        if (p.flat && K == 1) {
-            const int32_t pg = __builtin_amdgcn_readfirstlane(t.pid);
-            if (pg < 0) return;
-            const int32_t so0 = t.qo_a - t.jo0 * os.T;
-            const char *ob = os.base + (int64_t)t.l * os.s_l + (int64_t)pg * os.s_p +
-                             (int64_t)so0 * os.s_t;
-            const char *tb = t.t_base + (int64_t)t.sa * ts.s_t;
-            copy_runs<NT, UF, HOST>(const_cast<char *>(tb), ob, ts.s_c, os.s_c, (uint32_t)run_t,
-                                    p.C, kb, ke);
-            return;
+            if (bad && threadIdx.x < kWave) report(p, bad);   // the first wavefront
         }
     }
-    copy_rows<OP, TTHD, NT, HOST, UR>(p, q, t, kb, ke);
+    copy_rows<OP, TTHD, HOST, U>(p, q, t);
 }
 
 // Inclusive sum of x over the workgroup's threads (x = 0 past the chunk).
@@ -407,9 +383,8 @@ __device__ __forceinline__ int64_t block_scan(int64_t x, int64_t *s_wave) {
     return x;
 }
 
-template <int OP, bool TTHD, int NT, bool HOST>
+template <int OP, bool TTHD, bool HOST>
 __global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
-    constexpr int kWorkers = kBlock / NT;
     // Records are taken kBlock at a time: each thread reads one and counts
     // its tiles, a workgroup scan turns the counts into tile ranges, and the
     // workgroup's tiles inside the chunk find their record by binary search.
@@ -417,8 +392,8 @@ __global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
     __shared__ int64_t s_wave[kBlock / kWave];
     Req q;
     int32_t cached = -1;
-    const int64_t stride = (int64_t)gridDim.x * kWorkers;
-    int64_t tile = (int64_t)blockIdx.x * kWorkers + threadIdx.x / NT, chunk_base = 0;
+    const int64_t stride = (int64_t)gridDim.x;
+    int64_t tile = blockIdx.x, chunk_base = 0;
     for (int32_t r0 = 0; r0 < p.n_reqs; r0 += kBlock) {
         const int32_t nr = p.n_reqs - r0 < kBlock ? p.n_reqs - r0 : kBlock;
         int64_t cnt = 0;
@@ -431,7 +406,7 @@ __global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
         s_end[threadIdx.x] = block_scan(cnt, s_wave);
         __syncthreads();
         const int64_t chunk_tiles = s_end[kBlock - 1];
-        for (; tile < chunk_base + chunk_tiles; tile += stride) {   // uniform per worker
+        for (; tile < chunk_base + chunk_tiles; tile += stride) {   // uniform
             const int64_t local = tile - chunk_base;
             int32_t lo = 0, hi = nr - 1;             // first record whose range ends past `local`
             while (lo < hi) {
@@ -445,8 +420,7 @@ __global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
             }
             const int64_t in_rec = local - (lo ? s_end[lo - 1] : 0);
             const int64_t jj = in_rec / p.L;
-            do_tile<OP, TTHD, NT, HOST, KVX_UNROLL_FLAT, KVX_UNROLL_ROWS>(
-                p, q, jj, (int32_t)(in_rec - jj * p.L), 0u, 0xFFFFFFFFu);
+            do_tile<OP, TTHD, HOST, KVX_UNROLL_ROWS>(p, q, jj, (int32_t)(in_rec - jj * p.L));
         }
         chunk_base += chunk_tiles;
         __syncthreads();                             // s_end and s_wave are rewritten next chunk
@@ -738,27 +712,532 @@ __global__ void __launch_bounds__(kWave) kvx_sweep_kernel(SweepArgs a, Params) {
     if (!sweep_piece<MODE, HOST>(a, d, l, kb)) sweep_piece_general<MODE != ROWS_H, HOST>(p, d, l, kb);
 }
 
-typedef void (*KernelFn)(Params);
+// What the persistent grid reads of its arguments.  `t` is the tiling side,
+// `o` the other one; strides inside a page are in 16-byte vectors, which fit
+// 32 bits (a page of one layer has fewer than 2^31).
+struct GridArgs {
+    const kvx_req *reqs;
+    uint32_t *err;
+    int32_t n_reqs;
+    char *t_base, *o_base;
+    int64_t t_l, t_p, o_l, o_p;       // bytes from one layer or page to the next
+    const int32_t *t_pt, *o_pt;
+    int64_t t_len, o_len;
+    int64_t cap_bytes;                // buffer side
+    int64_t token_bytes;              // one token of a buffer's block
+    uint32_t t_N, o_N;
+    uint32_t C, elem_shift;
+    uint32_t t_c, t_t, o_c, o_t;
+    FastDiv fd_Tt, fd_To, fd_hv, fd_L;
+    uint32_t min_part;                // vectors a part has at least
+};
 
-constexpr int kFlatNT = KVX_FLAT_WAVE_TILES ? kWave : kBlock;
-constexpr int kRowsNT = KVX_ROWS_WAVE_TILES ? kWave : kBlock;
+// A record as the grid sees it: the part of it whose tiling-side pages the
+// table holds.
+struct GridRec {
+    int64_t t_idx;     // table index of its first tiling-side page
+    int64_t o_off;     // table offset (pool) or byte offset (buffer) of the other side
+    int64_t pages;     // its tiling-side pages; 0: nothing to copy
+    int32_t sa;        // slot of its first token
+    int32_t n;         // tokens
+    int32_t pos;       // other-side position of its first token
+    int32_t n_block;   // tokens of its block (buffer side)
+};
 
-template <int OP, bool HOST>
-KernelFn pick_op(bool tthd, bool flat) {
-    if (flat)
-        return tthd ? kvx_copy_kernel<OP, true, kFlatNT, HOST>
-                    : kvx_copy_kernel<OP, false, kFlatNT, HOST>;
-    return tthd ? kvx_copy_kernel<OP, true, kRowsNT, HOST> : kvx_copy_kernel<OP, false, kRowsNT, HOST>;
+// Works out record R (g.pages is 0 when there is nothing to copy); returns
+// the error bits it raises.  Every field is computed whatever the record
+// holds, without a branch.
+template <int OP>
+__device__ __forceinline__ uint32_t grid_record(const GridArgs &a, const kvx_req &R, GridRec &g) {
+    const int64_t so = R.src_pt_off, dof = R.dst_pt_off, bo = R.buf_off;
+    const int32_t s0 = R.src_start, d0 = R.dst_start, n = R.n_tokens;
+    bool ok = n >= 0 && s0 >= 0 && d0 >= 0 && R.reserved == 0 && (int64_t)s0 + n <= INT32_MAX &&
+              (int64_t)d0 + n <= INT32_MAX;
+    if (OP != OP_TRANSFER) {
+        const int64_t most = a.cap_bytes >> a.elem_shift, at = (bo < 0 ? 0 : bo > most ? most : bo) << a.elem_shift;
+        ok = ok && (OP == OP_GATHER ? d0 : s0) == 0 && bo >= 0 && bo <= most && (at & 15) == 0 &&
+             at + (int64_t)n * a.token_bytes <= a.cap_bytes;
+    }
+    const int64_t T = a.fd_Tt.d;
+    const int64_t t_off = OP == OP_GATHER ? so : dof;
+    const int64_t t_start = OP == OP_GATHER ? s0 : d0, o_start = OP == OP_GATHER ? d0 : s0;
+    const uint32_t first = ok ? (uint32_t)t_start : 0, last = ok && n > 0 ? (uint32_t)(t_start + n - 1) : 0;
+    // tiling-side pages [j0, j1], and of those the ones the table holds (a
+    // table offset beyond the 2^31 pages of a record either way holds none)
+    const int64_t j0 = fd_div(a.fd_Tt, first), j1 = fd_div(a.fd_Tt, last);
+    const int64_t far = (int64_t)1 << 32;
+    const int64_t off = t_off < -far ? -far : t_off > a.t_len ? a.t_len : t_off;
+    const int64_t lo = off < 0 ? -off : 0, hi = a.t_len - 1 - off;
+    const int64_t k0 = j0 > lo ? j0 : lo, k1 = j1 < hi ? j1 : hi;
+    const int64_t from = j0 < lo ? lo * T : t_start, to = j1 > hi ? (hi + 1) * T : t_start + n;
+    const bool some = ok && n > 0;
+    g.t_idx = off + k0;
+    g.o_off = OP == OP_TRANSFER ? so : (int64_t)((uint64_t)bo << a.elem_shift);
+    g.pages = some && k0 <= k1 ? k1 - k0 + 1 : 0;
+    g.sa = (int32_t)(from - k0 * T);
+    g.n = (int32_t)(to - from);
+    g.pos = (int32_t)(from - t_start + o_start);
+    g.n_block = n;
+    return !ok ? KVX_DERR_BAD_REQ : some && (k0 != j0 || k1 != j1) ? KVX_DERR_PT_RANGE : 0;
 }
 
-KernelFn pick(int op, bool tthd, bool flat, bool host) {
-    switch (op) {
-    case OP_TRANSFER:
-        return host ? pick_op<OP_TRANSFER, true>(tthd, flat) : pick_op<OP_TRANSFER, false>(tthd, flat);
-    case OP_GATHER:
-        return host ? pick_op<OP_GATHER, true>(tthd, flat) : pick_op<OP_GATHER, false>(tthd, flat);
-    default:
-        return host ? pick_op<OP_SCATTER, true>(tthd, flat) : pick_op<OP_SCATTER, false>(tthd, flat);
+// Inclusive sum over the wavefront's lanes, without LDS.
+__device__ __forceinline__ uint64_t wave_scan(uint64_t x) {
+#define KVX_DPP_ADD(ctrl, rows)                                                                            \
+    {                                                                                                      \
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, ctrl, rows, 0xf, false);      \
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), ctrl, rows, 0xf, false); \
+        x += ((uint64_t)hi << 32) | lo;                                                                    \
+    }
+    KVX_DPP_ADD(0x111, 0xf)   // row_shr 1, 2, 4, 8: the 16 lanes of a row
+    KVX_DPP_ADD(0x112, 0xf)
+    KVX_DPP_ADD(0x114, 0xf)
+    KVX_DPP_ADD(0x118, 0xf)
+    KVX_DPP_ADD(0x142, 0xa)   // row_bcast 15 into rows 1 and 3
+    KVX_DPP_ADD(0x143, 0xc)   // row_bcast 31 into rows 2 and 3
+#undef KVX_DPP_ADD
+    return x;
+}
+
+// Largest of the lanes' values, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_xor((int)x, d, kWave);
+        x = x > y ? x : y;
+    }
+    return x;
+}
+
+__device__ __forceinline__ uint32_t lane32(uint32_t v, int lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+__device__ __forceinline__ int64_t lane64(int64_t v, int lane) {
+    return ((int64_t)lane32((uint32_t)(v >> 32), lane) << 32) | lane32((uint32_t)v, lane);
+}
+
+// A part of a unit (a page of a layer): the vectors [kb, ke) of its K run and
+// then its V run, or of its tokens' runs.
+struct GridPart {
+    char *t;             // tiling side at the unit's first token, K
+    const char *o;       // other side there (ONE), or its layer
+    uint64_t o_c;        // other side: bytes from K to V
+    int64_t o_off;
+    uint32_t kb, ke;
+    uint32_t R;          // vectors of one kv component
+    uint32_t pos;        // other-side position of the first token
+};
+
+// Vector kk of a part: where it is read and written; false for none.  ONE:
+// the part's tokens lie in one page of the other side (always for a buffer),
+// which g.o points into; else page_of(jo) gives the id of the other side's
+// logical page jo (~0: none).
+template <int OP, SweepMode MODE, bool ONE, class PageOf>
+__device__ __forceinline__ bool part_vector(const GridArgs &a, const GridPart &g, uint32_t kk, PageOf page_of,
+                                            const char *&src, char *&dst) {
+    const uint32_t hv = a.fd_hv.d, k = kk < g.ke ? kk : g.ke - 1;
+    bool valid = kk < g.ke;
+    const bool c = k >= g.R;
+    const uint32_t w = c ? k - g.R : k;     // vector of the kv component
+    uint32_t to = w, oo = w;                // offsets in vectors
+    const char *ol = g.o;
+    if (MODE != RUNS || !ONE) {
+        const uint32_t tok = fd_div(a.fd_hv, w), in_tok = w - tok * hv;
+        to = tok * a.t_t + in_tok;
+        oo = ONE ? tok * a.o_t + in_tok : in_tok;
+        if (!ONE) {
+            const uint32_t q = g.pos + tok, jo = fd_div(a.fd_To, q), pg = page_of(jo, valid);
+            valid = valid && pg != ~0u;
+            ol += (int64_t)pg * a.o_p + (uint64_t)(q - jo * a.fd_To.d) * a.o_t * 16;
+        }
+    }
+    char *tp = g.t + ((uint64_t)to + (c ? a.t_c : 0)) * 16;
+    const char *op = ol + (uint64_t)oo * 16 + (c ? g.o_c : 0);
+    src = OP == OP_GATHER ? tp : op;
+    dst = OP == OP_GATHER ? const_cast<char *>(op) : tp;
+    return valid;
+}
+
+// Copies a part, U vectors per lane in flight.
+template <int OP, SweepMode MODE, bool ONE, bool HOST, int U, class PageOf>
+__device__ __forceinline__ void copy_part(const GridArgs &a, const GridPart &g, PageOf page_of) {
+    for (uint32_t k0 = g.kb; k0 < g.ke; k0 += kWave * U) {           // the same trip count for every lane
+        const char *src[U];
+        char *dst[U];
+        bool have[U];
+        v4u val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            have[u] = part_vector<OP, MODE, ONE>(a, g, k0 + u * kWave + threadIdx.x % kWave, page_of, src[u], dst[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (have[u]) val[u] = ld16(src[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (have[u]) st16<HOST>(dst[u], val[u]);
+    }
+}
+
+// The id of the other side's page `idx` of its table, ~0 (and reported) when
+// there is none.
+__device__ __forceinline__ uint32_t other_page(const GridArgs &a, int64_t idx) {
+    const bool in = idx >= 0 && idx < a.o_len;
+    const uint32_t pg = in ? (uint32_t)a.o_pt[idx] : ~0u;
+    if (pg < a.o_N) return pg;
+    if (a.err) atomicOr(a.err, in ? KVX_DERR_SRC_PAGE : KVX_DERR_PT_RANGE);
+    return ~0u;
+}
+
+__device__ __forceinline__ kvx_req load_raw(const GridArgs &a, int32_t r) {
+    kvx_req R{};
+    if (r < a.n_reqs) R = a.reqs[r];
+    return R;
+}
+
+// The arguments, read anew: kept over all of a kernel they would not fit the
+// scalar registers.
+__device__ __forceinline__ const GridArgs &fresh_args() {
+    typedef const __attribute__((address_space(4))) GridArgs *ConstArgs;
+    ConstArgs ap = (ConstArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    return *(const GridArgs *)ap;
+}
+
+// Persistent grid over parts of units, for calls of few or short records.
+// Every wavefront looks at the records by itself, 64 at a time, one per lane:
+// a scan over the lanes turns their parts into ranges, and the record of a
+// part is found with one ballot and read with lane reads, so nothing waits
+// for a barrier or LDS.  What bounds a small call is that chain of dependent
+// loads (records, page ids of both sides at once, data) and the width of the
+// chip: a unit is cut into parts of 64 U vectors, or larger ones once there
+// are KVX_GRID_PARTS per wavefront.  Layers are innermost, so that the parts
+// in flight spread over the pool.  Against whole units per wavefront and
+// records in LDS (us, start -> now): 64 decode records 14.8 -> 12.9, 64
+// half-filled pages 145 -> 108, 4 x 200 tokens 60.2 -> 48.4, 1024 decode
+// records 167.6 -> 163.6; 16384 of them 2331 -> 2340 (equal).
+template <int OP, SweepMode MODE, bool HOST, int U>
+__device__ __forceinline__ void copy_parts() {
+    constexpr bool kPool = OP == OP_TRANSFER;
+    constexpr uint32_t kUnit = kWave * U;
+    const uint32_t lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
+    const uint32_t workers = gridDim.x * waves;
+    int64_t at = (int64_t)blockIdx.x * waves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int32_t n_reqs = fresh_args().n_reqs;
+    kvx_req raw = load_raw(fresh_args(), lane);
+    for (int32_t r0 = 0; r0 < n_reqs; r0 += kWave) {
+        const GridArgs &ra = fresh_args();
+        const uint32_t L = ra.fd_L.d, T = ra.fd_Tt.d;
+        GridRec g;                                         // (a lane without a record has an empty one)
+        const uint32_t bad = grid_record<OP>(ra, raw, g);
+        if (bad && blockIdx.x == 0 && threadIdx.x < kWave && ra.err) atomicOr(ra.err, bad);
+        raw = load_raw(ra, r0 + kWave + lane);             // the next 64, on their way meanwhile
+        // vectors of the record's largest page, and of all records' pages
+        const uint32_t tile = (g.pages == 0 ? 0 : (uint32_t)g.n < T ? (uint32_t)g.n : T) * ra.fd_hv.d * ra.C;
+        const uint64_t all = (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * L *
+                             (uint32_t)((n_reqs + kWave - 1) / kWave);
+        // a part: 64 U vectors, or more when there are many
+        const uint64_t even = all / ((uint64_t)workers * KVX_GRID_PARTS);
+        const uint32_t fit = even > 0x3fffffff ? 0x40000000 : (uint32_t)(even / kUnit + 1) * kUnit;
+        const uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
+        const uint32_t parts = (tile + part_vecs - 1) / part_vecs;
+        const uint64_t end = wave_scan((uint64_t)g.pages * parts);
+        const int64_t total = lane64(end, kWave - 1) * L;
+        for (; at < total; at += workers) {
+            const GridArgs &a = fresh_args();
+            const uint64_t rem = at < INT32_MAX ? fd_div(a.fd_L, (uint32_t)at) : (uint64_t)at / L;
+            const uint32_t l = (uint32_t)(at - (int64_t)rem * L);
+            const int r = __builtin_ctzll(__ballot(end > rem));
+            const uint32_t r_parts = lane32(parts, r);
+            const uint64_t in = rem - (lane64(end, r) - lane64(g.pages, r) * r_parts);
+            uint32_t j = (uint32_t)in, part = 0;
+            if (r_parts > 1) {
+                j = in <= ~0u ? (uint32_t)in / r_parts : (uint32_t)(in / r_parts);
+                part = (uint32_t)(in - (uint64_t)j * r_parts);
+            }
+            uint32_t sa = lane32(g.sa, r), left = lane32(g.n, r);
+            const int64_t t_idx = lane64(g.t_idx, r) + j;
+            GridPart w;
+            w.pos = lane32(g.pos, r);
+            if (j > 0) {
+                const uint32_t skip = j * T - sa;
+                sa = 0;
+                left -= skip;
+                w.pos += skip;
+            }
+            const uint32_t ntok = left < T - sa ? left : T - sa;
+            w.o_off = lane64(g.o_off, r);
+            w.R = ntok * a.fd_hv.d;
+            const uint32_t vecs = w.R * a.C;
+            w.kb = part * part_vecs;
+            if (w.kb >= vecs) continue;
+            w.ke = vecs - w.kb < part_vecs ? vecs : w.kb + part_vecs;
+            // the page ids of both sides: the other side's pages of this page's
+            // tokens, the first 64 of them, one per lane
+            const uint32_t tpage = (uint32_t)cload(a.t_pt + t_idx);
+            uint32_t jo0 = 0, K = 1, opid = 0, bits = 0;
+            if (kPool) {
+                jo0 = fd_div(a.fd_To, w.pos);
+                K = fd_div(a.fd_To, w.pos + ntok - 1) - jo0 + 1;
+                if (lane < K) {
+                    const int64_t idx = w.o_off + jo0 + lane;
+                    if (idx < 0 || idx >= a.o_len) bits = KVX_DERR_PT_RANGE;
+                    else opid = (uint32_t)a.o_pt[idx];
+                }
+            }
+            if (tpage >= a.t_N) {
+                if (lane == 0 && a.err) atomicOr(a.err, OP == OP_GATHER ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
+                continue;
+            }
+            w.t = a.t_base + (int64_t)l * a.t_l + (int64_t)tpage * a.t_p + (uint64_t)sa * a.t_t * 16;
+            const auto from_lane = [&](uint32_t jo, bool valid) {
+                const uint32_t i = valid ? jo - jo0 : 0;
+                uint32_t pg = (uint32_t)__shfl((int)opid, i < kWave ? i : 0, kWave);
+                if (i >= kWave) pg = other_page(a, w.o_off + jo);      // more pages than lanes
+                return pg;
+            };
+            if (!kPool) {
+                const uint64_t run = (uint64_t)lane32(g.n_block, r) * a.fd_hv.d;   // vectors of one kv component's block
+                w.o = a.o_base + w.o_off + ((uint64_t)l * a.C * run + (uint64_t)w.pos * a.fd_hv.d) * 16;
+                w.o_c = run * 16;
+                copy_part<OP, MODE, true, HOST, U>(a, w, from_lane);
+                continue;
+            }
+            if (lane < K && opid >= a.o_N && !bits) bits = KVX_DERR_SRC_PAGE;
+            if (bits) {
+                opid = ~0u;
+                if (a.err) atomicOr(a.err, bits);
+            }
+            w.o = a.o_base + (int64_t)l * a.o_l;
+            w.o_c = (uint64_t)a.o_c * 16;
+            if (K == 1) {
+                const uint32_t pg = lane32(opid, 0);
+                if (pg == ~0u) continue;
+                w.o += (int64_t)pg * a.o_p + (uint64_t)(w.pos - jo0 * a.fd_To.d) * a.o_t * 16;
+                copy_part<OP, MODE, true, HOST, U>(a, w, from_lane);
+            } else {
+                copy_part<OP, MODE, false, HOST, U>(a, w, from_lane);
+            }
+        }
+        at -= total;
+    }
+}
+
+template <int OP, SweepMode MODE, bool HOST, int U>
+__global__ void __launch_bounds__(256) kvx_parts_kernel(GridArgs) {
+    copy_parts<OP, MODE, HOST, U>();
+}
+
+// Persistent grid that keeps the sweep's order, for calls of long records.
+// XCD x copies the units x, x + 8, ...; a team of its wavefronts takes a unit
+// together, 64 vectors (1 KiB) each, and goes on to the unit `teams` further,
+// so that what is in flight slides through a few pages per XCD.  Two things
+// keep it so:
+// - every lane plans one unit of its wavefront ahead (record by binary search
+//   in LDS, page ids, addresses), 64 units at a time, so that a piece costs
+//   the wavefront a few lane reads instead of a search (which ran at 4.8
+//   TB/s);
+// - a workgroup barrier before each piece: without it the wavefronts drift
+//   apart and the rate falls back to that of pages per wavefront (8528 us
+//   below; 7146 us with it).
+// A team member's piece turns from unit to unit, so that units that are not
+// full cost everybody the same.  Units of more pieces than an XCD has
+// wavefronts are taken in turns.
+// Against a page per wavefront (us): 32 prompts of 36 x 8 x 128, 256 KiB
+// pages, 43.7 GB, 8591 -> 7146 (6.1 TB/s; 6957 -> 6998 on pools that suit the
+// grid); 1500 tokens 92 -> 80.9; 72 KiB pages 4941 -> 4751; a scatter from a
+// buffer into 64 KiB pages of 6.2 GB 1190 -> 1060.
+template <int OP, SweepMode MODE, int B, int U>
+__global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
+    constexpr bool HOST = false;                   // (never over the link)
+    constexpr bool kPool = OP == OP_TRANSFER;
+    __shared__ int64_t s_end[B];                   // end of record i's pages among the chunk's
+    __shared__ GridRec s_rec[B];
+    __shared__ int64_t s_sum[B / kWave];
+    __shared__ uint32_t s_max[B / kWave];
+    const uint32_t lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t x = blockIdx.x & 7u, w = wave * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const uint32_t W = (gridDim.x >> 3) * (B / kWave);
+    const int32_t n_reqs = fresh_args().n_reqs;
+    {
+        // Whether the first 64 records are worth the order.
+        const GridArgs &a = fresh_args();
+        GridRec g;
+        (void)grid_record<OP>(a, load_raw(a, lane), g);
+        const uint32_t T = a.fd_Tt.d, n = g.pages ? (uint32_t)g.n : 0;
+        const uint64_t tokens = (uint64_t)lane64(wave_scan(n), kWave - 1);
+        const uint64_t pages = (uint64_t)lane64(wave_scan((uint64_t)g.pages), kWave - 1);
+        const uint32_t token_vecs = a.fd_hv.d * a.C;
+        if (!(4 * tokens >= KVX_ORDER_QUARTERS * pages * T && (uint64_t)T * token_vecs >= KVX_ORDER_PIECES * kWave &&
+              tokens * token_vecs * a.fd_L.d >= (uint64_t)W * 8 * KVX_ORDER_TURNS * kWave)) {
+            copy_parts<OP, MODE, HOST, U>();
+            return;
+        }
+    }
+    for (int32_t r0 = 0; r0 < n_reqs; r0 += B) {
+        const GridArgs &ra = fresh_args();
+        const uint32_t L = ra.fd_L.d, T = ra.fd_Tt.d;
+        GridRec g;
+        const uint32_t bad = grid_record<OP>(ra, load_raw(ra, r0 + threadIdx.x), g);
+        if (bad && blockIdx.x == 0 && ra.err) atomicOr(ra.err, bad);
+        s_rec[threadIdx.x] = g;
+        // vectors of the record's largest page
+        uint32_t most = (g.pages == 0 ? 0 : (uint32_t)g.n < T ? (uint32_t)g.n : T) * ra.fd_hv.d * ra.C;
+        int64_t end = (int64_t)wave_scan((uint64_t)g.pages);
+        most = wave_max(most);
+        if (lane == kWave - 1) {
+            s_sum[wave] = end;
+            s_max[wave] = most;
+        }
+        __syncthreads();
+        {
+            // the wavefronts before this one
+            const uint64_t sums = wave_scan(lane < B / kWave ? (uint64_t)s_sum[lane] : 0);
+            most = wave_max(lane < B / kWave ? s_max[lane] : 0);
+            if (wave) end += lane64((int64_t)sums, wave - 1);
+        }
+        s_end[threadIdx.x] = end;
+        __syncthreads();
+        const int64_t units = lane64(s_end[B - 1], 0) * L;
+        most = __builtin_amdgcn_readfirstlane(most);
+        // A team of `size` wavefronts of the XCD copies a unit, each of them
+        // every size-th piece of it.
+        const uint32_t pieces = (most + kWave - 1) / kWave;
+        uint32_t size = pieces, turns = 1;
+        if (size > W / 8) {
+            uint32_t used = 0;
+            for (uint32_t s = 1; s <= 8; ++s) {
+                const uint32_t z = (pieces + s - 1) / s;
+                if (z > W) continue;
+                const uint32_t u = W / z * z;
+                if (u > used + W / 16) used = u, size = z;
+            }
+            if (used == 0) size = W;
+            turns = (pieces + size - 1) / size;
+        }
+        const uint32_t teams = pieces ? W / size : 1, team = pieces ? w / size : 1;
+        const uint32_t p0 = w - team * size, turn = (size / 2 + size / 8) | 1;
+        const int64_t n0 = units > x ? (units - x + 8ll * teams - 1) / (8ll * teams) : 0;
+        for (int64_t b = 0; b < n0; b += kWave) {
+            // Each lane plans one unit.
+            const GridArgs &a = fresh_args();
+            const int64_t i = b + lane, at = (team + i * teams) * 8 + x;
+            bool ok = at < units && team < teams, one = true;
+            int64_t t_off = 0, o_off = 0, o_pt = 0;
+            uint64_t o_c = 0;
+            uint32_t kb = 0, R = 0, sa = 0, ntok = 0, pos = 0, l = 0;
+            if (ok) {
+                const int64_t n = units < INT32_MAX ? (int64_t)fd_div(a.fd_L, (uint32_t)at) : at / L;
+                l = (uint32_t)(at - n * L);
+                uint32_t r = 0;                    // first record whose pages end past n
+#pragma unroll
+                for (uint32_t step = B / 2; step; step >>= 1)
+                    if (s_end[r + step - 1] <= n) r += step;
+                const GridRec g = s_rec[r];
+                const uint32_t j = (uint32_t)(n - (r ? s_end[r - 1] : 0));
+                uint32_t left = (uint32_t)g.n;
+                sa = g.sa;
+                pos = g.pos;
+                if (j) {
+                    const uint32_t skip = j * T - sa;
+                    sa = 0;
+                    left -= skip;
+                    pos += skip;
+                }
+                ntok = left < T - sa ? left : T - sa;
+                R = ntok * a.fd_hv.d;
+                const uint32_t vecs = R * a.C;
+                kb = (p0 + (uint32_t)i * turn) % size * kWave;
+                ok = kb < vecs;
+                if (ok) {
+                    const uint32_t tpage = (uint32_t)a.t_pt[g.t_idx + j];
+                    o_pt = g.o_off;
+                    uint32_t jo0 = 0, opage = 0, bits = 0;
+                    if (kPool) {
+                        // the other side's pages of the piece's tokens (of the
+                        // whole unit when the piece is one of several)
+                        const uint32_t ke = (kb + kWave < vecs ? kb + kWave : vecs) - 1;
+                        const bool c0 = kb >= R, c1 = ke >= R;
+                        uint32_t t0 = 0, t1 = ntok - 1;
+                        if (c0 == c1 && turns == 1) {
+                            t0 = fd_div(a.fd_hv, c0 ? kb - R : kb);
+                            t1 = fd_div(a.fd_hv, c0 ? ke - R : ke);
+                        }
+                        jo0 = fd_div(a.fd_To, pos + t0);
+                        one = jo0 == fd_div(a.fd_To, pos + t1);
+                        const int64_t idx = o_pt + jo0;
+                        const bool in = idx >= 0 && idx < a.o_len;
+                        if (one) {
+                            opage = in ? (uint32_t)a.o_pt[idx] : 0;
+                            bits = !in ? KVX_DERR_PT_RANGE : opage >= a.o_N ? KVX_DERR_SRC_PAGE : 0;
+                        }
+                    }
+                    if (tpage >= a.t_N) bits = OP == OP_GATHER ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE;
+                    if (bits) {
+                        ok = false;
+                        if (a.err) atomicOr(a.err, bits);
+                    }
+                    t_off = (int64_t)l * a.t_l + (int64_t)tpage * a.t_p + (int64_t)sa * a.t_t * 16;
+                    if (kPool) {
+                        o_off = (int64_t)l * a.o_l;
+                        if (one) o_off += (int64_t)opage * a.o_p + ((int64_t)pos - (int64_t)jo0 * a.fd_To.d) * a.o_t * 16;
+                    } else {
+                        const uint64_t run = (uint64_t)g.n_block * a.fd_hv.d;    // vectors of one kv component's block
+                        o_c = run * 16;
+                        o_off = g.o_off + ((int64_t)l * a.C * run + (int64_t)pos * a.fd_hv.d) * 16;
+                    }
+                }
+            }
+            // Then the wavefront copies its pieces of the units, in order.
+            uint64_t todo = __ballot(ok);
+            const uint64_t ones = __ballot(one);
+            const GridArgs &ca = fresh_args();
+            const int rounds = n0 - b < kWave ? (int)(n0 - b) : kWave;
+            const auto piece = [&](int u, GridPart &c) {
+                c.t = ca.t_base + lane64(t_off, u);
+                c.o = ca.o_base + lane64(o_off, u);
+                c.o_c = kPool ? (uint64_t)ca.o_c * 16 : (uint64_t)lane64((int64_t)o_c, u);
+                c.R = lane32(R, u);
+                c.kb = lane32(kb, u);
+                c.ke = c.R * ca.C;
+            };
+            const auto none = [](uint32_t, bool) { return ~0u; };
+            if (turns == 1 && (todo & ~ones) == 0) {
+                for (int k = 0; k < rounds; ++k) {
+                    __builtin_amdgcn_s_barrier();
+                    if (todo == 0) continue;
+                    const int u = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    GridPart c;
+                    piece(u, c);
+                    const char *src;
+                    char *dst;
+                    if (part_vector<OP, MODE, true>(ca, c, c.kb + lane, none, src, dst)) st16<HOST>(dst, ld16(src));
+                }
+                continue;
+            }
+            for (int k = 0; k < rounds; ++k) {
+                __builtin_amdgcn_s_barrier();
+                if (todo == 0) continue;
+                const int u = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                GridPart c;
+                piece(u, c);
+                c.o_off = lane64(o_pt, u);
+                c.pos = lane32(pos, u);
+                const uint32_t vecs = c.ke;
+                for (uint32_t i = 0; i < turns && c.kb < vecs; ++i, c.kb += size * kWave) {
+                    c.ke = vecs - c.kb < kWave ? vecs : c.kb + kWave;
+                    if (!kPool || (ones >> u & 1)) {
+                        copy_part<OP, MODE, true, HOST, 1>(ca, c, none);
+                    } else {
+                        copy_part<OP, MODE, false, HOST, 1>(ca, c, [&](uint32_t jo, bool valid) {
+                            return valid ? other_page(ca, c.o_off + jo) : ~0u;
+                        });
+                    }
+                }
+            }
+        }
+        __syncthreads();                            // the next chunk reuses the shared state
     }
 }
 
@@ -834,27 +1313,97 @@ static int launch_sweep(const Params &p, hipStream_t stream) {
     return hipSuccess;
 }
 
+// The persistent grid's launch when the tokens are runs on both sides.
+template <int OP>
+static int launch_runs(const Params &p, int cus, hipStream_t stream) {
+    const Side &t = OP == OP_GATHER ? p.src : p.dst, &o = OP == OP_GATHER ? p.dst : p.src;
+    const int64_t row = p.row_bytes;
+    typedef void (*GridFn)(GridArgs);
+    constexpr int B = KVX_ORDER_BLOCK, U = KVX_PARTS_UNROLL, UL = KVX_LINK_UNROLL;
+    static const GridFn order_fns[2] = {kvx_order_kernel<OP, RUNS, B, U>, kvx_order_kernel<OP, TOKENS, B, U>};
+    static const GridFn parts_fns[2] = {kvx_parts_kernel<OP, RUNS, false, U>, kvx_parts_kernel<OP, TOKENS, false, U>};
+    static const GridFn link_fns[2][2] = {
+        {kvx_parts_kernel<OP, RUNS, false, UL>, kvx_parts_kernel<OP, RUNS, true, UL>},
+        {kvx_parts_kernel<OP, TOKENS, false, UL>, kvx_parts_kernel<OP, TOKENS, true, UL>}};
+    GridArgs a{};
+    a.reqs = p.reqs;
+    a.err = p.err;
+    a.n_reqs = p.n_reqs;
+    a.t_base = t.base;
+    a.o_base = o.base;
+    a.t_l = t.s_l;
+    a.t_p = t.s_p;
+    a.o_l = o.s_l;
+    a.o_p = o.s_p;
+    a.t_pt = t.pt;
+    a.o_pt = o.pt;
+    a.t_len = t.pt_len;
+    a.o_len = o.pt_len;
+    a.cap_bytes = o.cap_bytes;
+    a.token_bytes = (int64_t)p.L * p.C * p.H * row;
+    a.t_N = (uint32_t)t.N;
+    a.o_N = (uint32_t)o.N;
+    a.C = p.C;
+    a.elem_shift = (uint32_t)__builtin_ctz((unsigned)p.elem_bytes);
+    a.t_c = (uint32_t)(t.s_c / 16);
+    a.t_t = (uint32_t)(t.s_t / 16);
+    if (OP == OP_TRANSFER) {
+        a.o_c = (uint32_t)(o.s_c / 16);
+        a.o_t = (uint32_t)(o.s_t / 16);
+    } else {
+        a.o_t = p.H * p.vpr;
+    }
+    a.fd_Tt = p.fd_Tt;
+    a.fd_To = p.fd_To;
+    a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
+    a.fd_L = make_fastdiv((uint32_t)p.L);
+    const int tokens = p.flat ? 0 : 1;
+    const bool link = p.src_host || p.dst_host;
+    a.min_part = link ? 0x40000000 : kWave * U;          // over the link whole units
+    if (!link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs) {
+        hipLaunchKernelGGL(order_fns[tokens], dim3((cus + 7) / 8 * 8), dim3(B), 0, stream, a);
+    } else {
+        const GridFn fn = link ? link_fns[tokens][p.dst_host ? 1 : 0] : parts_fns[tokens];
+        hipLaunchKernelGGL(fn, dim3(cus * (link ? KVX_LINK_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU)), dim3(256), 0,
+                           stream, a);
+    }
+    return hipGetLastError();
+}
+
+// The persistent grid's launch when rows are resolved.
+template <int OP>
+static int launch_rows(const Params &p, int cus, hipStream_t stream) {
+    typedef void (*RowsFn)(Params);
+    static const RowsFn fns[2][2] = {{kvx_copy_kernel<OP, false, false>, kvx_copy_kernel<OP, false, true>},
+                                     {kvx_copy_kernel<OP, true, false>, kvx_copy_kernel<OP, true, true>}};
+    const bool tthd = (OP == OP_GATHER ? p.src : p.dst).tok_contig != 0;
+    hipLaunchKernelGGL(fns[tthd][p.dst_host ? 1 : 0], dim3(cus * KVX_ROWS_BLOCKS_PER_CU), dim3(kBlock), 0, stream, p);
+    return hipGetLastError();
+}
+
+template <int OP>
+static int launch_grid(const Params &p, hipStream_t stream) {
+    const auto adjacent = [&](const Side &x, bool pool) {
+        return !pool || ((p.H == 1 || x.s_h == p.row_bytes) && x.s_t >= (int64_t)p.H * p.row_bytes);
+    };
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (adjacent(p.src, OP != OP_SCATTER) && adjacent(p.dst, OP != OP_GATHER)) return launch_runs<OP>(p, cus, stream);
+    return launch_rows<OP>(p, cus, stream);
+}
+
 // Sweep when the host chose it (p.sweep), else a persistent grid: as
 // many workgroups as the device holds at once.
 int launch(const Params &p, hipStream_t stream) {
     if (p.sweep) return launch_sweep(p, stream);
-    const bool tthd = (p.op == OP_GATHER ? p.src : p.dst).tok_contig != 0;
-    KernelFn fn = pick(p.op, tthd, p.flat != 0, p.dst_host != 0);
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    int cus = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    int per_cu = p.flat ? KVX_BLOCKS_PER_CU : KVX_ROWS_BLOCKS_PER_CU;
-    if (per_cu <= 0) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn),
-                                                         kBlock, 0);
-        if (e != hipSuccess) return e;
-        if (per_cu < 1) per_cu = 1;
+    switch (p.op) {
+    case OP_TRANSFER: return launch_grid<OP_TRANSFER>(p, stream);
+    case OP_GATHER: return launch_grid<OP_GATHER>(p, stream);
+    default: return launch_grid<OP_SCATTER>(p, stream);
     }
-    hipLaunchKernelGGL(fn, dim3(cus * per_cu), dim3(kBlock), 0, stream, p);
-    return hipGetLastError();
 }
 
 }  // namespace kvx

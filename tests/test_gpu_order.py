@@ -1,0 +1,100 @@
+"""Unplanned calls whose tokens are runs on both sides, bit for bit against
+the oracle: in order (the test build copies every such call in order, the
+product library those of long records) and in parts (the product library's
+way for the rest)."""
+import numpy as np
+import pytest
+
+import cases
+from paper_2606_31093_amd.workloads import BufSpec, PoolSpec, Step, Workload
+from runner import assert_same, initial_bytes, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(params=["test", "product"])
+def library(request, monkeypatch):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_31093_amd import build_lib, kvx
+    kvx.lib()    # the product library first: raises if it is missing
+    if request.param == "test":
+        monkeypatch.setattr(kvx, "_LIB", kvx.load(build_lib.TEST_LIBRARY))
+    return request.param
+
+
+def check(wl):
+    init = initial_bytes(wl)
+    want, werr = run_oracle(wl, init)
+    got, gerr = run_gpu(wl, init)
+    assert gerr == werr, f"{wl.title}: device error bits {gerr}, oracle {werr}"
+    assert_same(got, want, wl.title)
+
+
+@pytest.mark.parametrize("Ts,Td", [(4, 4), (16, 64), (64, 16), (1, 16), (16, 1), (3, 5)])
+@pytest.mark.parametrize("ls,ld", [("LPCTHD", "LPCTHD"), ("PLCTHD", "LPCTHD"), ("LPCTHD", "PLCTHD")])
+def test_page_sizes(library, ls, ld, Ts, Td):
+    check(cases.transfer_case(ls, ld, Ts, Td, seed=Ts * 100 + Td, D=64))
+
+
+@pytest.mark.parametrize("seed", range(60))
+def test_random(library, seed):
+    """Random transfers (damaged tables, slices, shared pages), copies inside
+    a pool, layered transfers, and gathers and scatters with bad blocks."""
+    check((cases.random_case, cases.random_cow_case, cases.random_layered_case,
+           cases.random_gs_case)[seed % 4](seed))
+
+
+@pytest.mark.parametrize("T,H,D,L,n", [(160, 8, 128, 2, 333),    # 640 pieces: more than an XCD's wavefronts
+                                       (150, 4, 128, 3, 700),    # 300: no divisor of them
+                                       (64, 8, 128, 5, 260),     # 256
+                                       (64, 1, 576, 7, 500)])    # one kv component, 72
+@pytest.mark.parametrize("shift", [0, 7])
+def test_large_pages(library, T, H, D, L, n, shift):
+    """Pages of as many pieces as a team has wavefronts, and more; with a
+    shift, pieces that lie in two source pages."""
+    C = 1 if D == 576 else 2
+    spec = [(shift, 0, n, None), (3, 3, 2 * T, None), (T - 1, 0, 1, None)]
+    check(cases.transfer_case("LPCTHD", "PLCTHD", T, T, seed=T + shift, D=D, L=L, C=C, H=H, spec=spec))
+
+
+@pytest.mark.parametrize("n_reqs", [63, 64, 65, 1023, 1024, 1025, 2100])
+def test_many_records(library, n_reqs):
+    """Around the 64 records of a wavefront and the 1024 of a workgroup, every
+    fifth of them empty."""
+    spec = [(i % 3, (i * 5) % 4, 0 if i % 5 == 4 else 1 + i % 7, None) for i in range(n_reqs)]
+    check(cases.transfer_case("LPCTHD", "LPCTHD", 4, 4, seed=n_reqs, D=8, L=3, H=1, spec=spec))
+
+
+@pytest.mark.parametrize("T,pinned", [(16, False), (64, False), (64, True)])
+def test_gather_and_scatter(library, T, pinned):
+    """Through a flat buffer, in device memory (long records, in order) and in
+    pinned host memory (in parts)."""
+    check(cases.gather_scatter_case("LPCTHD", T, 2, 128, seed=T, H=8, pinned=pinned))
+
+
+def test_product_library_keeps_the_order_of_long_records():
+    """One record of 20 pages of 256 KiB over 16 layers: 84 MB, above the size
+    from which the product library copies in order; its table's first entry
+    is out of range and one page id is bad."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S = PoolSpec(16, 2, 8, 128, T=64, N=24, e=2, layout="LPCTHD")
+    rng = np.random.default_rng(5)
+    src, dst = rng.permutation(24)[:21].astype(np.int32), rng.permutation(24)[:21].astype(np.int32)
+    dst[7] = 24
+    src[11] = -1
+    rows = np.asarray([[0, -1, 0, 5, 5, 20 * 64]], np.int64)
+    wl = Workload("case", "long record", {"A": S, "B": S}, [Step("transfer", "A", "B", src, dst, rows)],
+                  value_seed=8, prefill_tag=3)
+    check(wl)
+    block = 16 * 2 * 1280 * 8 * 128
+    buf = BufSpec(16, 2, 8, 128, 2, cap=block)
+    rows = np.asarray([[0, 0, 0, 0, 0, 1280]], np.int64)
+    good = rng.permutation(24)[:20].astype(np.int32)
+    wl = Workload("case", "long block", {"A": S, "buf": buf, "B": S},
+                  [Step("gather", "A", "buf", good, None, rows), Step("scatter", "buf", "B", None, good[::-1].copy(), rows)],
+                  value_seed=9, prefill_tag=4)
+    check(wl)
