@@ -34,6 +34,7 @@
 #include <stdlib.h>
 
 #include "kvx_hash.h"
+#include "kvx_internal.h"
 
 namespace kvx {
 namespace {
@@ -314,10 +315,8 @@ __global__ void __launch_bounds__(kWave * (1 + kDW)) kvx_page_hash_kernel(HashPa
 
 int launch_hash(const HashParams &p0, hipStream_t stream) {
     if (p0.n_reqs == 0) return hipSuccess;
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    int cus = 0;
+    const hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;
     HashParams p = p0;
     // Empty polls in a row the chain allows: far more than one page's digest

@@ -114,6 +114,9 @@ inline uint32_t sweep_pieces(const Params &p, int64_t page_slots) {
     return (uint32_t)((vecs + 63) / 64);
 }
 
+// Compute units of the current device.
+hipError_t device_cus(int *cus);
+
 // Launch on `stream`; returns a hipError_t value.
 int launch(const Params &p, hipStream_t stream);
 

@@ -28,6 +28,8 @@
 // 6.3 TB/s, depending on where the pools sit in physical memory, when every
 // wavefront walks through a page of its own.
 
+#include <atomic>
+
 #include "kvx_internal.h"
 
 #ifndef KVX_UNROLL_ROWS
@@ -1381,15 +1383,25 @@ static int launch_rows(const Params &p, int cus, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Compute units of the current device, asked for once per device.
+hipError_t device_cus(int *cus) {
+    static std::atomic<int> seen[64];
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 64 && (*cus = seen[dev].load(std::memory_order_relaxed)) > 0) return hipSuccess;
+    const hipError_t q = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (q == hipSuccess && dev < 64) seen[dev].store(*cus, std::memory_order_relaxed);
+    return q;
+}
+
 template <int OP>
 static int launch_grid(const Params &p, hipStream_t stream) {
     const auto adjacent = [&](const Side &x, bool pool) {
         return !pool || ((p.H == 1 || x.s_h == p.row_bytes) && x.s_t >= (int64_t)p.H * p.row_bytes);
     };
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    int cus = 0;
+    const hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;
     if (adjacent(p.src, OP != OP_SCATTER) && adjacent(p.dst, OP != OP_GATHER)) return launch_runs<OP>(p, cus, stream);
     return launch_rows<OP>(p, cus, stream);

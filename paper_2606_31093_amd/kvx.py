@@ -18,6 +18,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -39,6 +40,8 @@ REQ_DTYPE = np.dtype([("src_pt_off", "<i8"), ("dst_pt_off", "<i8"), ("buf_off", 
                       ("src_start", "<i4"), ("dst_start", "<i4"), ("n_tokens", "<i4"),
                       ("reserved", "<i4")])
 
+
+REQ_DTYPE_SIZE = REQ_DTYPE.itemsize
 
 HASH_REQ_DTYPE = np.dtype([("payload_off", "<i8"), ("out_off", "<i8"), ("seed", "<u8"),
                            ("n_positions", "<i4"), ("reserved", "<i4")])
@@ -152,7 +155,17 @@ def load(path: str) -> ctypes.CDLL:
     L.kvx_launch_choice.restype = ctypes.c_int
     L.kvx_last_launch.argtypes = []
     L.kvx_last_launch.restype = ctypes.c_int
+    # The copy calls once more, with descriptors as packed bytes: a ctypes
+    # structure per descriptor and call took half of a small call's time.
+    for f in _PACKED:
+        g = L["kvx_" + f]
+        g.argtypes = [vp if t in (pp, bp, sp) else t for t in getattr(L, "kvx_" + f).argtypes]
+        g.restype = ctypes.c_int
+        setattr(L, "packed_" + f, g)
     return L
+
+
+_PACKED = ("transfer", "transfer_slice", "transfer_layered", "transfer_planned", "transfer_layered_planned", "gather", "scatter", "gather_slice", "scatter_slice")
 
 
 # ---------------------------------------------------------------------------
@@ -225,7 +238,8 @@ def pool_bytes(spec) -> int:
 def _stream(stream) -> int | None:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        c = torch._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -236,48 +250,86 @@ def _check(status: int) -> None:
         raise KvxError(status, lib().kvx_last_error().decode())
 
 
+_POOL_PACK = struct.Struct("=Q8i").pack
+_BUF_PACK = struct.Struct("=Q6iq").pack
+_SLICE_PACK = struct.Struct("=10i").pack
+
+
 def _n_reqs(reqs) -> int:
-    nbytes = reqs.numel() * reqs.element_size()
-    if nbytes % REQ_DTYPE.itemsize:
+    n, rest = divmod(reqs.nbytes, REQ_DTYPE_SIZE)
+    if rest:
         raise ValueError("reqs must hold whole 40-byte kvx_req records")
     if not reqs.is_contiguous():
         raise ValueError("reqs must be contiguous")
-    return nbytes // REQ_DTYPE.itemsize
-
-
-def _len(t) -> int:
-    return 0 if t is None else t.numel()
+    return n
 
 
 def _table(t, name: str):
-    """A page table: a contiguous tensor of 32-bit entries (or None)."""
-    if t is not None and not isinstance(t, int):
-        if t.element_size() != 4 or t.is_floating_point() or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous int32 tensor (got {t.dtype})")
-    return t
+    """A page table, a contiguous tensor of 32-bit entries (or None): its
+    address and length."""
+    if t is None:
+        return None, 0
+    if isinstance(t, int):
+        raise ValueError(f"{name} must be a contiguous int32 tensor (got an address)")
+    if t.element_size() != 4 or t.is_floating_point() or not t.is_contiguous():
+        raise ValueError(f"{name} must be a contiguous int32 tensor (got {t.dtype})")
+    return t.data_ptr(), t.numel()
 
 
 def _err_word(t):
-    """The optional device error word: one 32-bit integer."""
-    if t is not None and not isinstance(t, int):
-        if t.element_size() != 4 or t.is_floating_point() or t.numel() < 1:
-            raise ValueError(f"dev_err must be a 32-bit integer tensor (got {t.dtype})")
-    return t
-
-
-def _need(t, nbytes: int, name: str) -> None:
-    """A tensor argument must hold at least the bytes its descriptor names."""
+    """The optional device error word, one 32-bit integer: its address."""
     if t is None or isinstance(t, int):
-        return
-    have = t.numel() * t.element_size()
+        return t
+    if t.element_size() != 4 or t.is_floating_point() or t.numel() < 1:
+        raise ValueError(f"dev_err must be a 32-bit integer tensor (got {t.dtype})")
+    return t.data_ptr()
+
+
+def _need(t, nbytes: int, name: str) -> int:
+    """The address of a tensor argument, which must hold at least the bytes
+    its descriptor names."""
+    if t is None:
+        return 0
+    if isinstance(t, int):
+        return t
+    have = t.nbytes
     if have < nbytes:
         raise ValueError(f"{name} holds {have} bytes, its descriptor needs {nbytes}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
+    return t.data_ptr()
 
 
-def _pool_nbytes(spec) -> int:
-    return spec.L * spec.C * spec.H * spec.D * spec.T * spec.N * spec.e
+def _pool_arg(spec, t, name: str) -> bytes:
+    """The kvx_pool of a pool argument, packed."""
+    L, C, H, D, T, N, e = spec.L, spec.C, spec.H, spec.D, spec.T, spec.N, spec.e
+    ptr = _need(t, L * C * H * D * T * N * e, name)
+    layout = spec.layout
+    code = LAYOUTS[layout] if isinstance(layout, str) else int(layout)
+    try:
+        return _POOL_PACK(ptr, L, C, H, D, T, N, e, code)
+    except struct.error:               # a value of another width: as ctypes takes it
+        return bytes(pool_desc(spec, t))
+
+
+def _buf_arg(spec, t, name: str) -> bytes:
+    """The kvx_buf of a buffer argument, packed."""
+    cap, e = spec.cap, spec.e
+    ptr = _need(t, cap * e, name)
+    try:
+        return _BUF_PACK(ptr, spec.L, spec.C, spec.H, spec.D, e, 0, cap)
+    except struct.error:
+        return bytes(buf_desc(spec, t))
+
+
+def _slice_arg(sl) -> bytes:
+    """A kvx_slice, packed."""
+    if type(sl) is tuple and len(sl) == 9:
+        try:
+            return _SLICE_PACK(*sl, 0)
+        except struct.error:
+            pass
+    return bytes(slice_desc(sl))
 
 
 def kvx_transfer(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, dev_err=None,
@@ -285,26 +337,25 @@ def kvx_transfer(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, dev_err=Non
     """Pool -> pool (see kvx_transfer in include/kvx.h).  ``src_pt`` /
     ``dst_pt`` are int32 device tensors, ``reqs`` a device tensor from
     ``device_reqs``, ``dev_err`` an optional int32/uint32 device word."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    S, D = pool_desc(src_spec, src), pool_desc(dst_spec, dst)
-    _table(src_pt, "src_pt"), _table(dst_pt, "dst_pt"), _err_word(dev_err)
-    _check(lib().kvx_transfer(ctypes.byref(S), ctypes.byref(D), _ptr(src_pt), _len(src_pt),
-                              _ptr(dst_pt), _len(dst_pt), _ptr(reqs), _n_reqs(reqs),
-                              _ptr(dev_err), _stream(stream)))
+    S, D = _pool_arg(src_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    spt, n_spt = _table(src_pt, "src_pt")
+    dpt, n_dpt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_transfer(S, D, spt, n_spt, dpt, n_dpt, reqs.data_ptr(), _n_reqs(reqs), err,
+                                 _stream(stream)))
 
 
 def kvx_transfer_slice(src, src_spec, dst, dst_spec, sl, src_pt, dst_pt, reqs, dev_err=None,
                        stream=None) -> None:
     """Slice of a pool -> slice of another pool (see kvx_transfer_slice in
     include/kvx.h).  ``sl`` is a ``Slice`` or the nine range fields."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    S, D, X = pool_desc(src_spec, src), pool_desc(dst_spec, dst), slice_desc(sl)
-    _table(src_pt, "src_pt"), _table(dst_pt, "dst_pt"), _err_word(dev_err)
-    _check(lib().kvx_transfer_slice(ctypes.byref(S), ctypes.byref(D), ctypes.byref(X),
-                                    _ptr(src_pt), _len(src_pt), _ptr(dst_pt), _len(dst_pt),
-                                    _ptr(reqs), _n_reqs(reqs), _ptr(dev_err), _stream(stream)))
+    S, D = _pool_arg(src_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    X = _slice_arg(sl)
+    spt, n_spt = _table(src_pt, "src_pt")
+    dpt, n_dpt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_transfer_slice(S, D, X, spt, n_spt, dpt, n_dpt, reqs.data_ptr(), _n_reqs(reqs), err,
+                                       _stream(stream)))
 
 
 def kvx_transfer_planned(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, plan, plan_pages,
@@ -314,21 +365,19 @@ def kvx_transfer_planned(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, pla
     ``plan_pages``, ``plan_tokens`` its totals, as ``device_plan`` returns.  ``sl`` is an optional
     slice (nine range fields or a ``Slice``); ``library`` a build loaded with
     ``load`` (default: ``lib()``)."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    S, D = pool_desc(src_spec, src), pool_desc(dst_spec, dst)
-    X = ctypes.byref(slice_desc(sl)) if sl is not None else None
-    _table(src_pt, "src_pt"), _table(dst_pt, "dst_pt"), _err_word(dev_err)
+    S, D = _pool_arg(src_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    X = _slice_arg(sl) if sl is not None else None
+    spt, n_spt = _table(src_pt, "src_pt")
+    dpt, n_dpt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
     n = _n_reqs(reqs)
     if plan is not None and not isinstance(plan, int):
-        if not plan.is_contiguous() or plan.numel() * plan.element_size() < plan_bytes(n, plan_pages):
+        if not plan.is_contiguous() or plan.nbytes < plan_bytes(n, plan_pages):
             raise ValueError("plan must be a contiguous tensor of KVX_PLAN_BYTES(n_reqs, plan_pages) "
                              "bytes")
     L = library or lib()
-    status = L.kvx_transfer_planned(ctypes.byref(S), ctypes.byref(D), X, _ptr(src_pt), _len(src_pt),
-                                    _ptr(dst_pt), _len(dst_pt), _ptr(reqs), n, _ptr(plan),
-                                    int(plan_pages), int(plan_tokens), _ptr(dev_err),
-                                    _stream(stream))
+    status = L.packed_transfer_planned(S, D, X, spt, n_spt, dpt, n_dpt, reqs.data_ptr(), n, _ptr(plan),
+                                       int(plan_pages), int(plan_tokens), err, _stream(stream))
     if status != 0:
         raise KvxError(status, L.kvx_last_error().decode())
 
@@ -403,17 +452,15 @@ def kvx_transfer_layered(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, lay
     include/kvx.h).  ``events`` are ``torch.cuda.Event`` objects (or raw
     hipEvent_t handles), one per layer group; the library records events[g]
     on the stream once group g has been copied."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    _table(src_pt, "src_pt"), _table(dst_pt, "dst_pt"), _err_word(dev_err)
+    S, D = _pool_arg(src_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    X = None if sl is None else _slice_arg(sl)
+    spt, n_spt = _table(src_pt, "src_pt")
+    dpt, n_dpt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
     st = _stream(stream)
     arr, n_ev = _event_handles(events, st, stream)
-    S, D = pool_desc(src_spec, src), pool_desc(dst_spec, dst)
-    X = None if sl is None else ctypes.byref(slice_desc(sl))
-    _check(lib().kvx_transfer_layered(ctypes.byref(S), ctypes.byref(D), X, _ptr(src_pt),
-                                      _len(src_pt), _ptr(dst_pt), _len(dst_pt), _ptr(reqs),
-                                      _n_reqs(reqs), int(layers_per_group), arr, n_ev,
-                                      _ptr(dev_err), st))
+    _check(lib().packed_transfer_layered(S, D, X, spt, n_spt, dpt, n_dpt, reqs.data_ptr(), _n_reqs(reqs),
+                                         int(layers_per_group), arr, n_ev, err, st))
 
 
 def kvx_transfer_layered_planned(src, src_spec, dst, dst_spec, src_pt, dst_pt, reqs, layers_per_group,
@@ -421,45 +468,40 @@ def kvx_transfer_layered_planned(src, src_spec, dst, dst_spec, src_pt, dst_pt, r
                                  stream=None, library=None) -> None:
     """kvx_transfer_layered with a plan (see kvx_transfer_layered_planned
     in include/kvx.h); the plan as ``device_plan`` returns it."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    _table(src_pt, "src_pt"), _table(dst_pt, "dst_pt"), _err_word(dev_err)
+    S, D = _pool_arg(src_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    X = None if sl is None else _slice_arg(sl)
+    spt, n_spt = _table(src_pt, "src_pt")
+    dpt, n_dpt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
     n = _n_reqs(reqs)
     if plan is not None and not isinstance(plan, int):
-        if not plan.is_contiguous() or plan.numel() * plan.element_size() < plan_bytes(n, plan_pages):
+        if not plan.is_contiguous() or plan.nbytes < plan_bytes(n, plan_pages):
             raise ValueError("plan must be a contiguous tensor of KVX_PLAN_BYTES(n_reqs, plan_pages) "
                              "bytes")
     st = _stream(stream)
     arr, n_ev = _event_handles(events, st, stream)
-    S, D = pool_desc(src_spec, src), pool_desc(dst_spec, dst)
-    X = None if sl is None else ctypes.byref(slice_desc(sl))
     L = library or lib()
-    status = L.kvx_transfer_layered_planned(ctypes.byref(S), ctypes.byref(D), X, _ptr(src_pt),
-                                            _len(src_pt), _ptr(dst_pt), _len(dst_pt), _ptr(reqs), n,
-                                            int(layers_per_group), arr, n_ev, _ptr(plan),
-                                            int(plan_pages), int(plan_tokens), _ptr(dev_err), st)
+    status = L.packed_transfer_layered_planned(S, D, X, spt, n_spt, dpt, n_dpt, reqs.data_ptr(), n,
+                                               int(layers_per_group), arr, n_ev, _ptr(plan), int(plan_pages),
+                                               int(plan_tokens), err, st)
     if status != 0:
         raise KvxError(status, L.kvx_last_error().decode())
 
 
 def kvx_gather(src, src_spec, dst, buf_spec, src_pt, reqs, dev_err=None, stream=None) -> None:
     """Pool -> flat buffer (see kvx_gather in include/kvx.h)."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, buf_spec.cap * buf_spec.e, "dst")
-    S, B = pool_desc(src_spec, src), buf_desc(buf_spec, dst)
-    _table(src_pt, "src_pt"), _err_word(dev_err)
-    _check(lib().kvx_gather(ctypes.byref(S), ctypes.byref(B), _ptr(src_pt), _len(src_pt),
-                            _ptr(reqs), _n_reqs(reqs), _ptr(dev_err), _stream(stream)))
+    S, B = _pool_arg(src_spec, src, "src"), _buf_arg(buf_spec, dst, "dst")
+    pt, n_pt = _table(src_pt, "src_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_gather(S, B, pt, n_pt, reqs.data_ptr(), _n_reqs(reqs), err, _stream(stream)))
 
 
 def kvx_scatter(src, buf_spec, dst, dst_spec, dst_pt, reqs, dev_err=None, stream=None) -> None:
     """Flat buffer -> pool (see kvx_scatter in include/kvx.h)."""
-    _need(src, buf_spec.cap * buf_spec.e, "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    B, D = buf_desc(buf_spec, src), pool_desc(dst_spec, dst)
-    _table(dst_pt, "dst_pt"), _err_word(dev_err)
-    _check(lib().kvx_scatter(ctypes.byref(B), ctypes.byref(D), _ptr(dst_pt), _len(dst_pt),
-                             _ptr(reqs), _n_reqs(reqs), _ptr(dev_err), _stream(stream)))
+    B, D = _buf_arg(buf_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    pt, n_pt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_scatter(B, D, pt, n_pt, reqs.data_ptr(), _n_reqs(reqs), err, _stream(stream)))
 
 
 def kvx_gather_slice(src, src_spec, dst, buf_spec, sl, src_pt, reqs, dev_err=None,
@@ -467,26 +509,23 @@ def kvx_gather_slice(src, src_spec, dst, buf_spec, sl, src_pt, reqs, dev_err=Non
     """Slice of a pool -> flat buffer holding exactly the slice (see
     kvx_gather_slice in include/kvx.h).  ``sl`` is a ``Slice`` or the nine
     range fields."""
-    _need(src, _pool_nbytes(src_spec), "src")
-    _need(dst, buf_spec.cap * buf_spec.e, "dst")
-    S, B, X = pool_desc(src_spec, src), buf_desc(buf_spec, dst), slice_desc(sl)
-    _table(src_pt, "src_pt"), _err_word(dev_err)
-    _check(lib().kvx_gather_slice(ctypes.byref(S), ctypes.byref(B), ctypes.byref(X), _ptr(src_pt),
-                                  _len(src_pt), _ptr(reqs), _n_reqs(reqs), _ptr(dev_err),
-                                  _stream(stream)))
+    S, B = _pool_arg(src_spec, src, "src"), _buf_arg(buf_spec, dst, "dst")
+    X = _slice_arg(sl)
+    pt, n_pt = _table(src_pt, "src_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_gather_slice(S, B, X, pt, n_pt, reqs.data_ptr(), _n_reqs(reqs), err, _stream(stream)))
 
 
 def kvx_scatter_slice(src, buf_spec, dst, dst_spec, sl, dst_pt, reqs, dev_err=None,
                       stream=None) -> None:
     """Flat buffer holding exactly a slice -> that slice of a pool (see
     kvx_scatter_slice in include/kvx.h)."""
-    _need(src, buf_spec.cap * buf_spec.e, "src")
-    _need(dst, _pool_nbytes(dst_spec), "dst")
-    B, D, X = buf_desc(buf_spec, src), pool_desc(dst_spec, dst), slice_desc(sl)
-    _table(dst_pt, "dst_pt"), _err_word(dev_err)
-    _check(lib().kvx_scatter_slice(ctypes.byref(B), ctypes.byref(D), ctypes.byref(X), _ptr(dst_pt),
-                                   _len(dst_pt), _ptr(reqs), _n_reqs(reqs), _ptr(dev_err),
-                                   _stream(stream)))
+    B, D = _buf_arg(buf_spec, src, "src"), _pool_arg(dst_spec, dst, "dst")
+    X = _slice_arg(sl)
+    pt, n_pt = _table(dst_pt, "dst_pt")
+    err = _err_word(dev_err)
+    _check(lib().packed_scatter_slice(B, D, X, pt, n_pt, reqs.data_ptr(), _n_reqs(reqs), err,
+                                      _stream(stream)))
 
 
 def pack_hash_reqs(rows) -> np.ndarray:
