@@ -18,13 +18,14 @@ LIBRARY = os.path.join(PKG, "libkvx.so")
 # The test build: its hash chain gives up after one empty poll, planned
 # transfers of any size take the sweep launch (its launch choice starts as
 # KVX_CHOOSE_SWEEP), with at most 2048 workgroups, so that larger cases take
-# several launches, and unplanned runs of any size are copied in order.
+# several launches, unplanned runs of any size are copied in order, and
+# unplanned rows of any size by teams of wavefronts.
 # These are compile-time options: the product library has
 # no switch for them.
 TEST_LIBRARY = os.path.join(PKG, "libkvx_test.so")
 TEST_DEFINES = ("KVX_HASH_IDLE_POLLS=1", "KVX_SWEEP_MIN_BYTES=0", "KVX_SWEEP_MAX_BLOCKS=2048",
                 "KVX_LAUNCH_CHOICE_DEFAULT=1", "KVX_ORDER_PAGES=0", "KVX_ORDER_PIECES=0",
-                "KVX_ORDER_QUARTERS=0", "KVX_ORDER_TURNS=0")
+                "KVX_ORDER_QUARTERS=0", "KVX_ORDER_TURNS=0", "KVX_TEAM_KIB=0")
 SOURCES = [os.path.join(CSRC, "kvx_kernels.hip"), os.path.join(CSRC, "kvx_hash.hip"),
            os.path.join(CSRC, "kvx_api.cpp")]
 HEADERS = [os.path.join(INCLUDE, "kvx.h"), os.path.join(CSRC, "kvx_internal.h"),

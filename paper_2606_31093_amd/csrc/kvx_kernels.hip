@@ -11,16 +11,14 @@
 // The unit of work is one page of the tiling side in one layer; the tiling
 // side is the destination pool for transfer and
 // scatter (each unit then writes one destination page of one layer, and no
-// two units write the same bytes) and the source pool for gather.  Four
+// two units write the same bytes) and the source pool for gather.  Three
 // kernels share the work out:
 // - kvx_sweep_kernel: a planned transfer, one workgroup of one wavefront per
 //   kilobyte of a unit, started in order by the hardware;
 // - kvx_order_kernel: unplanned calls of long records whose tokens are runs
 //   on both sides, a persistent grid that keeps that order;
-// - kvx_parts_kernel: the other unplanned calls of runs (few or short
-//   records, the host link), a persistent grid over parts of units;
-// - kvx_copy_kernel: unplanned calls that resolve rows (a head-major side), a
-//   persistent grid over whole units.
+// - kvx_parts_kernel: the other unplanned calls (few or short records, rows to
+//   resolve, the host link), a persistent grid over parts of units.
 //
 // Order matters because of the memory, not of the caches: nothing is re-read.
 // A bare copy of random 256 KiB pages moves 6.6 TB/s (read + write) when the
@@ -32,9 +30,6 @@
 
 #include "kvx_internal.h"
 
-#ifndef KVX_UNROLL_ROWS
-#define KVX_UNROLL_ROWS 4
-#endif
 #ifndef KVX_NT
 #define KVX_NT 1   // streaming (non-temporal) loads and stores: nothing is re-read
 #endif
@@ -43,9 +38,6 @@
 #endif
 #ifndef KVX_NT_STORE
 #define KVX_NT_STORE KVX_NT
-#endif
-#ifndef KVX_ROWS_BLOCKS_PER_CU
-#define KVX_ROWS_BLOCKS_PER_CU 3  // grid of launches that resolve rows (measured best)
 #endif
 // kvx_parts_kernel: workgroups of 256 threads per CU, and 16-byte vectors in
 // flight per lane.  64 decode records (1-4 tokens of 36 x 8 x 128): 7 x 4
@@ -60,6 +52,23 @@
 // layers: 108 us with 32, 116 with 8.
 #ifndef KVX_GRID_PARTS
 #define KVX_GRID_PARTS 32
+#endif
+// Unplanned calls that resolve rows: from KVX_TEAM_KIB KiB per wavefront of the
+// grid on, four wavefronts share a part, KVX_TEAM_BLOCKS_PER_CU workgroups per
+// CU, KVX_TEAM_PARTS parts per wavefront.  A wavefront to itself walks through
+// a page of its own, and thousands of pages at once run at the memory's random
+// rate (head-major to token-major, 8.1 GB: 1634 us; with teams 1513).  A call
+// that small anyway has more parts than teams without them (200 tokens of
+// 36 x 8 x 128: 17 us with a wavefront per part, 31.5 with teams that search
+// the records in LDS).
+#ifndef KVX_TEAM_KIB
+#define KVX_TEAM_KIB 8
+#endif
+#ifndef KVX_TEAM_PARTS
+#define KVX_TEAM_PARTS 1
+#endif
+#ifndef KVX_TEAM_BLOCKS_PER_CU
+#define KVX_TEAM_BLOCKS_PER_CU 3
 #endif
 // The same over the host link: whole units, 8 vectors per lane (4: 1.8%
 // slower; units in parts 1.8%).
@@ -101,7 +110,6 @@
 namespace kvx {
 namespace {
 
-constexpr int kBlock = 256;   // rows: the threads that copy a tile
 constexpr int kWave = 64;
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
@@ -146,291 +154,34 @@ __device__ __forceinline__ void report(const Params &p, uint32_t bits) {
     if (p.err) atomicOr(p.err, bits);
 }
 
-// A request as one tile walk sees it.
+// A record as the plan's check sees it.
 struct Req {
-    int64_t t_pt_off, o_pt_off;  // table offsets of the tiling / other side
-    int64_t blk;                 // buffer block offset in bytes
-    int64_t tiles;               // tiles this request contributes
-    int64_t pages;               // tiling-side pages it touches (tiles = pages * layers)
+    int64_t t_pt_off, o_pt_off;  // table offsets of the destination / source
+    int64_t pages;               // destination pages it touches
     int32_t t_start, o_start, n;
-    int32_t j0;                  // first tiling-side page (logical)
+    int32_t j0;                  // first destination page (logical)
 };
 
-__device__ __forceinline__ bool block_fits(const Side &b, int64_t off, int32_t n,
-                                           int64_t token_bytes, int32_t e) {
-    if (off < 0 || off > b.cap_bytes / e) return false;
-    const int64_t start = off * e;
-    return (start & 15) == 0 && start + (int64_t)n * token_bytes <= b.cap_bytes;
-}
-
-template <int OP>
 __device__ __forceinline__ bool load_req(const Params &p, int32_t r, Req &q) {
     const kvx_req &R = p.reqs[r];
-    const int64_t so = R.src_pt_off, dof = R.dst_pt_off, bo = R.buf_off;
-    const int32_t s0 = R.src_start, d0 = R.dst_start, n = R.n_tokens;
-    bool ok = n >= 0 && s0 >= 0 && d0 >= 0 && R.reserved == 0 &&
-              (int64_t)s0 + n <= INT32_MAX && (int64_t)d0 + n <= INT32_MAX;
-    const int64_t token_bytes = (int64_t)p.L * p.C * p.H * p.row_bytes;
-    if (OP == OP_GATHER) ok = ok && d0 == 0 && block_fits(p.dst, bo, n, token_bytes, p.elem_bytes);
-    if (OP == OP_SCATTER) ok = ok && s0 == 0 && block_fits(p.src, bo, n, token_bytes, p.elem_bytes);
-    if (!ok) {
-        q.tiles = 0;
-        q.pages = 0;
+    q.t_pt_off = R.dst_pt_off;
+    q.o_pt_off = R.src_pt_off;
+    q.t_start = R.dst_start;
+    q.o_start = R.src_start;
+    q.n = R.n_tokens;
+    q.j0 = 0;
+    q.pages = 0;
+    if (q.n < 0 || q.o_start < 0 || q.t_start < 0 || R.reserved != 0 ||
+        (int64_t)q.o_start + q.n > INT32_MAX || (int64_t)q.t_start + q.n > INT32_MAX)
         return false;
-    }
-    const bool tsrc = OP == OP_GATHER;
-    q.t_pt_off = tsrc ? so : dof;
-    q.o_pt_off = tsrc ? dof : so;
-    q.t_start = tsrc ? s0 : d0;
-    q.o_start = tsrc ? d0 : s0;
-    q.n = n;
-    q.blk = bo * p.elem_bytes;
-    if (n == 0) {
-        q.tiles = 0;
-        q.pages = 0;
-        q.j0 = 0;
-        return true;
-    }
-    const int32_t j0 = (int32_t)fd_div(p.fd_Tt, (uint32_t)q.t_start);
-    const int32_t j1 = (int32_t)fd_div(p.fd_Tt, (uint32_t)(q.t_start + n - 1));
-    q.j0 = j0;
-    q.pages = j1 - j0 + 1;
-    q.tiles = q.pages * p.L;
+    if (q.n == 0) return true;
+    q.j0 = (int32_t)fd_div(p.fd_Tt, (uint32_t)q.t_start);
+    q.pages = (int32_t)fd_div(p.fd_Tt, (uint32_t)(q.t_start + q.n - 1)) - q.j0 + 1;
     return true;
 }
 
-// Everything a tile's row loop needs, fixed for the tile.
-struct Tile {
-    const char *t_base;   // tiling side at (l, page, c = 0, slot = 0, h = 0)
-    int32_t sa, sb;       // tiling-side slots [sa, sb) of this tile
-    int32_t ntok;         // sb - sa
-    // buffer other side
-    const char *o_row0;   // other side at (l, c = 0, token of slot sa, h = 0)
-    int64_t o_sc;         // buffer: bytes between kv components of the block
-    // pool other side
-    int32_t qo_a;         // other-side position of slot sa
-    int32_t jo0;          // other-side logical page of qo_a
-    int32_t pid;          // this lane's piece page id (-1: invalid / unused)
-    int32_t l;
-};
-
-// General row-resolving copy.  Vectors are enumerated in (c, slot, h, v)
-// order when the tiling side is token-major (its memory order), else in
-// blocks of slots as described below, with the slots outside [sa, sb)
-// masked.
-template <int OP, bool TTHD, bool HOST, int U>
-__device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const Tile &t) {
-    constexpr bool kTileSrc = OP == OP_GATHER;
-    constexpr bool kOtherBuf = OP != OP_TRANSFER;
-    const Side &ts = kTileSrc ? p.src : p.dst;
-    const Side &os = kTileSrc ? p.dst : p.src;
-    const uint32_t H = p.H, vpr = p.vpr, row = p.row_bytes;
-    // A head-major tiling side takes its vectors in (c, slot block, h, slot,
-    // v) order over the blocks of SB slots that meet [sa, sb): the tiling
-    // side's writes are SB-row runs, and the other side's reads, whose
-    // consecutive heads are adjacent, fill whole slots within a few passes.
-    // (Page order, one head at a time, left the reads 256-byte pieces a
-    // kilobyte apart: 11% slower on a 16-token -> 64-token relayout.)
-    constexpr uint32_t SB = KVX_SLOT_BLOCK;
-    const uint32_t blk0 = (uint32_t)t.sa / SB, nblk = ((uint32_t)t.sb - 1) / SB - blk0 + 1;
-    const uint32_t rows_c = TTHD ? (uint32_t)t.ntok * H : H * nblk * SB;
-    const uint32_t total = rows_c * vpr * (uint32_t)p.C;
-    const char *o_l = os.base + (int64_t)t.l * os.s_l;
-    // The trip count is the same for every lane: the page-id broadcast below
-    // reads other lanes, which must all still be active.
-    for (uint32_t kb = 0; kb < total; kb += kBlock * U) {
-        const char *src[U];
-        char *dst[U];
-        bool ok[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t kk = kb + threadIdx.x + u * kBlock;
-            const uint32_t k = kk < total ? kk : total - 1;
-            bool valid = kk < total;
-            const uint32_t rw = fd_div(p.fd_vpr, k);
-            const uint32_t v = k - rw * vpr;
-            const uint32_t c = rw >= rows_c;
-            const uint32_t rr = rw - c * rows_c;
-            uint32_t h, slot;
-            if (TTHD) {
-                const uint32_t tt = fd_div(p.fd_H, rr);
-                h = rr - tt * H;
-                slot = t.sa + tt;
-            } else {
-                const uint32_t q1 = rr / SB;
-                const uint32_t blk = fd_div(p.fd_H, q1);
-                h = q1 - blk * H;
-                slot = (blk0 + blk) * SB + (rr - q1 * SB);
-                valid = valid && slot >= (uint32_t)t.sa && slot < (uint32_t)t.sb;
-            }
-            const int32_t tt = (int32_t)slot - t.sa;  // token index within the tile
-            const char *ta = t.t_base + c * ts.s_c + (int64_t)slot * ts.s_t +
-                             (int64_t)h * ts.s_h + v * 16;
-            const char *oa;
-            if (kOtherBuf) {
-                oa = t.o_row0 + c * t.o_sc + (int64_t)tt * H * row + h * row + v * 16;
-            } else {
-                const uint32_t qo = (uint32_t)(t.qo_a + tt);
-                const uint32_t jo = fd_div(p.fd_To, qo);
-                const uint32_t so = qo - jo * (uint32_t)os.T;
-                const uint32_t piece = jo - (uint32_t)t.jo0;
-                int32_t pg = __shfl(t.pid, piece < kWave ? piece : kWave - 1, kWave);
-                if (valid && piece >= kWave) {
-                    // More pieces than lanes: resolve this row's page directly.
-                    const int64_t idx = q.o_pt_off + jo;
-                    pg = -1;
-                    if (idx < 0 || idx >= os.pt_len) {
-                        report(p, KVX_DERR_PT_RANGE);
-                    } else {
-                        const int32_t id = os.pt[idx];
-                        if (id < 0 || id >= os.N) report(p, KVX_DERR_SRC_PAGE);
-                        else pg = id;
-                    }
-                }
-                valid = valid && pg >= 0;
-                oa = o_l + (int64_t)pg * os.s_p + c * os.s_c + (int64_t)so * os.s_t +
-                     (int64_t)h * os.s_h + v * 16;
-            }
-            ok[u] = valid;
-            src[u] = kTileSrc ? ta : oa;
-            dst[u] = const_cast<char *>(kTileSrc ? oa : ta);
-        }
-        v4u val[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (ok[u]) val[u] = ld16(src[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (ok[u]) st16<HOST>(dst[u], val[u]);
-    }
-}
-
-// Tile (request q, its tiling-side page jj, layer l), U vectors per thread in
-// flight.
-template <int OP, bool TTHD, bool HOST, int U>
-__device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t jj, int32_t layer) {
-    constexpr bool kTileSrc = OP == OP_GATHER;
-    constexpr bool kOtherBuf = OP != OP_TRANSFER;
-    const Side &ts = kTileSrc ? p.src : p.dst;
-    const Side &os = kTileSrc ? p.dst : p.src;
-
-    Tile t;
-    t.l = layer;
-    const int64_t j = q.j0 + jj;
-    const int64_t page_lo = j * ts.T;
-    const int64_t qa = page_lo > q.t_start ? page_lo : q.t_start;
-    const int64_t q_end = (int64_t)q.t_start + q.n;
-    const int64_t qb = page_lo + ts.T < q_end ? page_lo + ts.T : q_end;
-    t.sa = (int32_t)(qa - page_lo);
-    t.sb = (int32_t)(qb - page_lo);
-    t.ntok = t.sb - t.sa;
-
-    // Tiling-side page (one per tile; a uniform load).
-    const int64_t tidx = q.t_pt_off + j;
-    if (tidx < 0 || tidx >= ts.pt_len) {
-        if (threadIdx.x == 0) report(p, KVX_DERR_PT_RANGE);
-        return;
-    }
-    const int32_t tpage = ts.pt[tidx];
-    if (tpage < 0 || tpage >= ts.N) {
-        if (threadIdx.x == 0) report(p, kTileSrc ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
-        return;
-    }
-    t.t_base = ts.base + (int64_t)t.l * ts.s_l + (int64_t)tpage * ts.s_p;
-
-    if (kOtherBuf) {
-        const int64_t H_row = (int64_t)p.H * p.row_bytes;
-        const int64_t i0 = qa - q.t_start;
-        t.o_sc = (int64_t)q.n * H_row;
-        t.o_row0 = os.base + q.blk + (int64_t)t.l * p.C * t.o_sc + i0 * H_row;
-        t.pid = -1;
-        t.qo_a = 0;
-        t.jo0 = 0;
-    } else {
-        const int32_t delta = q.o_start - q.t_start;
-        t.qo_a = (int32_t)qa + delta;
-        t.jo0 = (int32_t)fd_div(p.fd_To, (uint32_t)t.qo_a);
-        const int32_t jo1 = (int32_t)fd_div(p.fd_To, (uint32_t)((int32_t)qb - 1 + delta));
-        const int32_t K = jo1 - t.jo0 + 1;
-        const int32_t lane = threadIdx.x & (kWave - 1);
-        t.pid = -1;
-        if (lane < K) {
-            const int64_t idx = q.o_pt_off + t.jo0 + lane;
-            uint32_t bad = 0;
-            if (idx < 0 || idx >= os.pt_len) {
-                bad = KVX_DERR_PT_RANGE;
-            } else {
-                const int32_t id = os.pt[idx];
-                if (id < 0 || id >= os.N) bad = KVX_DERR_SRC_PAGE;
-                else t.pid = id;
-            }
-            if (bad && threadIdx.x < kWave) report(p, bad);   // the first wavefront
-        }
-    }
-    copy_rows<OP, TTHD, HOST, U>(p, q, t);
-}
-
-// Inclusive sum of x over the workgroup's threads (x = 0 past the chunk).
-// Every thread of the workgroup must call it: it contains barriers.
-__device__ __forceinline__ int64_t block_scan(int64_t x, int64_t *s_wave) {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
-    }
-    if (lane == kWave - 1) s_wave[wid] = x;
-    __syncthreads();
-    for (int w = 0; w < wid; ++w) x += s_wave[w];
-    return x;
-}
-
-template <int OP, bool TTHD, bool HOST>
-__global__ void __launch_bounds__(kBlock) kvx_copy_kernel(Params p) {
-    // Records are taken kBlock at a time: each thread reads one and counts
-    // its tiles, a workgroup scan turns the counts into tile ranges, and the
-    // workgroup's tiles inside the chunk find their record by binary search.
-    __shared__ int64_t s_end[kBlock];   // end (exclusive) of record i's tiles in the chunk
-    __shared__ int64_t s_wave[kBlock / kWave];
-    Req q;
-    int32_t cached = -1;
-    const int64_t stride = (int64_t)gridDim.x;
-    int64_t tile = blockIdx.x, chunk_base = 0;
-    for (int32_t r0 = 0; r0 < p.n_reqs; r0 += kBlock) {
-        const int32_t nr = p.n_reqs - r0 < kBlock ? p.n_reqs - r0 : kBlock;
-        int64_t cnt = 0;
-        if ((int32_t)threadIdx.x < nr) {
-            Req mine;
-            if (!load_req<OP>(p, r0 + threadIdx.x, mine) && blockIdx.x == 0)
-                report(p, KVX_DERR_BAD_REQ);
-            cnt = mine.tiles;
-        }
-        s_end[threadIdx.x] = block_scan(cnt, s_wave);
-        __syncthreads();
-        const int64_t chunk_tiles = s_end[kBlock - 1];
-        for (; tile < chunk_base + chunk_tiles; tile += stride) {   // uniform
-            const int64_t local = tile - chunk_base;
-            int32_t lo = 0, hi = nr - 1;             // first record whose range ends past `local`
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (s_end[mid] > local) hi = mid;
-                else lo = mid + 1;
-            }
-            if (r0 + lo != cached) {
-                load_req<OP>(p, r0 + lo, q);
-                cached = r0 + lo;
-            }
-            const int64_t in_rec = local - (lo ? s_end[lo - 1] : 0);
-            const int64_t jj = in_rec / p.L;
-            do_tile<OP, TTHD, HOST, KVX_UNROLL_ROWS>(p, q, jj, (int32_t)(in_rec - jj * p.L));
-        }
-        chunk_base += chunk_tiles;
-        __syncthreads();                             // s_end and s_wave are rewritten next chunk
-    }
-}
-
 // Lane k's row of a sweep piece: kv component c, slot, head h, vector v of
-// the row, in the vector order of copy_rows (TOKENS: token by token; else, for
+// the row, in the vector order of a unit (TOKENS: token by token; else, for
 // a head-major destination, in blocks of KVX_SWEEP_SLOT_BLOCK slots); valid is
 // cleared for a masked slot of a head-major destination.
 template <bool TOKENS>
@@ -536,7 +287,7 @@ __device__ __forceinline__ void sweep_piece_general(const Params &p, const kvx_p
 }
 
 // One piece of the sweep: the vectors [kb, kb + 64) of page slot d of layer
-// l, one per lane, in the vector order of copy_rows.  The common path, a piece
+// l, one per lane, in the vector order of its mode.  The common path, a piece
 // whose rows lie in one source page with every index and page id in range,
 // needs the two page ids and nothing else, read through the scalar cache;
 // returns false for any other piece, before anything was copied or reported.
@@ -613,7 +364,7 @@ __device__ __forceinline__ bool slot_agrees(const Params &p, int64_t qi, const k
     const int32_t r = d.req;
     if (r < 0 || r >= p.n_reqs) return false;
     Req q;
-    if (!load_req<OP_TRANSFER>(p, r, q)) return false;
+    if (!load_req(p, r, q)) return false;
     const int64_t jj = qi - p.prefix[r];
     if (jj < 0 || qi >= p.prefix[r + 1] || jj >= q.pages) return false;
     const int64_t j = (int64_t)q.j0 + jj, page_lo = j * p.dst.T;
@@ -638,7 +389,7 @@ __device__ __forceinline__ void sweep_check(const Params &p, uint32_t b, uint32_
         bad_plan = bad_plan || !slot_agrees(p, qi, p.slots[qi]);
     for (int64_t r = first; r < p.n_reqs; r += step) {
         Req mine;
-        if (!load_req<OP_TRANSFER>(p, (int32_t)r, mine)) report(p, KVX_DERR_BAD_REQ);
+        if (!load_req(p, (int32_t)r, mine)) report(p, KVX_DERR_BAD_REQ);
         bad_plan = bad_plan || p.prefix[r + 1] - p.prefix[r] != mine.pages;
     }
     if (bad_plan) report(p, KVX_DERR_BAD_PLAN);
@@ -731,7 +482,10 @@ struct GridArgs {
     uint32_t C, elem_shift;
     uint32_t t_c, t_t, o_c, o_t;
     FastDiv fd_Tt, fd_To, fd_hv, fd_L;
+    uint32_t t_h, o_h;                // rows only
+    FastDiv fd_vpr, fd_H;             // rows only
     uint32_t min_part;                // vectors a part has at least
+    uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part
 };
 
 // A record as the grid sees it: the part of it whose tiling-side pages the
@@ -828,7 +582,49 @@ struct GridPart {
     uint32_t kb, ke;
     uint32_t R;          // vectors of one kv component
     uint32_t pos;        // other-side position of the first token
+    uint32_t sa, ntok;   // ROWS_H: slot of the first token, tokens
 };
+
+// Slots that a unit's vectors enumerate: its tokens, or (ROWS_H) the whole
+// blocks of KVX_SLOT_BLOCK slots that they meet.
+template <SweepMode MODE>
+__device__ __forceinline__ uint32_t unit_slots(uint32_t sa, uint32_t ntok) {
+    constexpr uint32_t SB = KVX_SLOT_BLOCK;
+    return MODE == ROWS_H ? ((sa + ntok - 1) / SB - sa / SB + 1) * SB : ntok;
+}
+
+// The most of them that a page of a record has.
+template <SweepMode MODE>
+__device__ __forceinline__ uint32_t record_slots(const GridRec &g, uint32_t T) {
+    constexpr uint32_t SB = KVX_SLOT_BLOCK;
+    if (g.pages == 0) return 0;
+    const uint32_t n = (uint32_t)g.n < T ? (uint32_t)g.n : T;
+    if (MODE != ROWS_H) return n;
+    const uint32_t some = (n - 1) / SB + 2, all = (T - 1) / SB + 1;
+    return (some < all ? some : all) * SB;
+}
+
+// Token (from the unit's first one; out of range for a masked slot), head and
+// vector of the row of vector w of a kv component.
+template <SweepMode MODE>
+__device__ __forceinline__ void unit_row(const GridArgs &a, uint32_t sa, uint32_t w, uint32_t &tok, uint32_t &h,
+                                         uint32_t &v) {
+    constexpr uint32_t SB = KVX_SLOT_BLOCK;
+    if (MODE == ROWS_H) {
+        const uint32_t rw = fd_div(a.fd_vpr, w), q1 = rw / SB, blk = fd_div(a.fd_H, q1);
+        v = w - rw * a.fd_vpr.d;
+        h = q1 - blk * a.fd_H.d;
+        tok = (sa / SB + blk) * SB + (rw - q1 * SB) - sa;
+    } else {
+        tok = fd_div(a.fd_hv, w);
+        v = w - tok * a.fd_hv.d;
+        h = 0;
+        if (MODE == ROWS_T) {
+            h = fd_div(a.fd_vpr, v);
+            v -= h * a.fd_vpr.d;
+        }
+    }
+}
 
 // Vector kk of a part: where it is read and written; false for none.  ONE:
 // the part's tokens lie in one page of the other side (always for a buffer),
@@ -837,16 +633,22 @@ struct GridPart {
 template <int OP, SweepMode MODE, bool ONE, class PageOf>
 __device__ __forceinline__ bool part_vector(const GridArgs &a, const GridPart &g, uint32_t kk, PageOf page_of,
                                             const char *&src, char *&dst) {
-    const uint32_t hv = a.fd_hv.d, k = kk < g.ke ? kk : g.ke - 1;
+    const uint32_t k = kk < g.ke ? kk : g.ke - 1;
     bool valid = kk < g.ke;
     const bool c = k >= g.R;
     const uint32_t w = c ? k - g.R : k;     // vector of the kv component
     uint32_t to = w, oo = w;                // offsets in vectors
     const char *ol = g.o;
     if (MODE != RUNS || !ONE) {
-        const uint32_t tok = fd_div(a.fd_hv, w), in_tok = w - tok * hv;
-        to = tok * a.t_t + in_tok;
-        oo = ONE ? tok * a.o_t + in_tok : in_tok;
+        uint32_t tok, h, v;
+        unit_row<MODE>(a, g.sa, w, tok, h, v);
+        if (MODE == ROWS_H) valid = valid && tok < g.ntok;
+        to = tok * a.t_t + v;
+        oo = ONE ? tok * a.o_t + v : v;
+        if (MODE == ROWS_T || MODE == ROWS_H) {
+            to += h * a.t_h;
+            oo += h * a.o_h;
+        }
         if (!ONE) {
             const uint32_t q = g.pos + tok, jo = fd_div(a.fd_To, q), pg = page_of(jo, valid);
             valid = valid && pg != ~0u;
@@ -860,17 +662,19 @@ __device__ __forceinline__ bool part_vector(const GridArgs &a, const GridPart &g
     return valid;
 }
 
-// Copies a part, U vectors per lane in flight.
+// Copies a part, U vectors per lane in flight: thread `me` of the `span` that
+// share it.
 template <int OP, SweepMode MODE, bool ONE, bool HOST, int U, class PageOf>
-__device__ __forceinline__ void copy_part(const GridArgs &a, const GridPart &g, PageOf page_of) {
-    for (uint32_t k0 = g.kb; k0 < g.ke; k0 += kWave * U) {           // the same trip count for every lane
+__device__ __forceinline__ void copy_part(const GridArgs &a, const GridPart &g, uint32_t me, uint32_t span,
+                                          PageOf page_of) {
+    for (uint32_t k0 = g.kb; k0 < g.ke; k0 += span * U) {            // the same trip count for every lane
         const char *src[U];
         char *dst[U];
         bool have[U];
         v4u val[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            have[u] = part_vector<OP, MODE, ONE>(a, g, k0 + u * kWave + threadIdx.x % kWave, page_of, src[u], dst[u]);
+            have[u] = part_vector<OP, MODE, ONE>(a, g, k0 + u * span + me, page_of, src[u], dst[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (have[u]) val[u] = ld16(src[u]);
@@ -905,7 +709,8 @@ __device__ __forceinline__ const GridArgs &fresh_args() {
     return *(const GridArgs *)ap;
 }
 
-// Persistent grid over parts of units, for calls of few or short records.
+// Persistent grid over parts of units, for calls of few or short records and
+// for those that resolve rows.
 // Every wavefront looks at the records by itself, 64 at a time, one per lane:
 // a scan over the lanes turns their parts into ranges, and the record of a
 // part is found with one ballot and read with lane reads, so nothing waits
@@ -920,10 +725,12 @@ __device__ __forceinline__ const GridArgs &fresh_args() {
 template <int OP, SweepMode MODE, bool HOST, int U>
 __device__ __forceinline__ void copy_parts() {
     constexpr bool kPool = OP == OP_TRANSFER;
-    constexpr uint32_t kUnit = kWave * U;
+    constexpr uint32_t kUnit = kWave * U, kTeam = 4;
     const uint32_t lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t workers = gridDim.x * waves;
-    int64_t at = (int64_t)blockIdx.x * waves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t team = 1, me = lane;
+    int64_t at = (int64_t)blockIdx.x * waves + wave;
     const int32_t n_reqs = fresh_args().n_reqs;
     kvx_req raw = load_raw(fresh_args(), lane);
     for (int32_t r0 = 0; r0 < n_reqs; r0 += kWave) {
@@ -934,17 +741,22 @@ __device__ __forceinline__ void copy_parts() {
         if (bad && blockIdx.x == 0 && threadIdx.x < kWave && ra.err) atomicOr(ra.err, bad);
         raw = load_raw(ra, r0 + kWave + lane);             // the next 64, on their way meanwhile
         // vectors of the record's largest page, and of all records' pages
-        const uint32_t tile = (g.pages == 0 ? 0 : (uint32_t)g.n < T ? (uint32_t)g.n : T) * ra.fd_hv.d * ra.C;
+        const uint32_t tile = record_slots<MODE>(g, T) * ra.fd_hv.d * ra.C;
         const uint64_t all = (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * L *
                              (uint32_t)((n_reqs + kWave - 1) / kWave);
+        if (r0 == 0 && (MODE == ROWS_T || MODE == ROWS_H) && all >= ra.team_min) {
+            team = kTeam;
+            me = threadIdx.x % (kTeam * kWave);
+            at /= kTeam;
+        }
         // a part: 64 U vectors, or more when there are many
-        const uint64_t even = all / ((uint64_t)workers * KVX_GRID_PARTS);
-        const uint32_t fit = even > 0x3fffffff ? 0x40000000 : (uint32_t)(even / kUnit + 1) * kUnit;
+        const uint64_t even = all / ((uint64_t)workers * (team == 1 ? KVX_GRID_PARTS : KVX_TEAM_PARTS));
+        const uint32_t fit = even > 0x3fffffff ? 0x40000000 : (uint32_t)(even / (kUnit * team) + 1) * kUnit * team;
         const uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
         const uint32_t parts = (tile + part_vecs - 1) / part_vecs;
         const uint64_t end = wave_scan((uint64_t)g.pages * parts);
         const int64_t total = lane64(end, kWave - 1) * L;
-        for (; at < total; at += workers) {
+        for (; at < total; at += workers / team) {
             const GridArgs &a = fresh_args();
             const uint64_t rem = at < INT32_MAX ? fd_div(a.fd_L, (uint32_t)at) : (uint64_t)at / L;
             const uint32_t l = (uint32_t)(at - (int64_t)rem * L);
@@ -968,7 +780,9 @@ __device__ __forceinline__ void copy_parts() {
             }
             const uint32_t ntok = left < T - sa ? left : T - sa;
             w.o_off = lane64(g.o_off, r);
-            w.R = ntok * a.fd_hv.d;
+            w.sa = sa;
+            w.ntok = ntok;
+            w.R = unit_slots<MODE>(sa, ntok) * a.fd_hv.d;
             const uint32_t vecs = w.R * a.C;
             w.kb = part * part_vecs;
             if (w.kb >= vecs) continue;
@@ -1001,7 +815,7 @@ __device__ __forceinline__ void copy_parts() {
                 const uint64_t run = (uint64_t)lane32(g.n_block, r) * a.fd_hv.d;   // vectors of one kv component's block
                 w.o = a.o_base + w.o_off + ((uint64_t)l * a.C * run + (uint64_t)w.pos * a.fd_hv.d) * 16;
                 w.o_c = run * 16;
-                copy_part<OP, MODE, true, HOST, U>(a, w, from_lane);
+                copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
                 continue;
             }
             if (lane < K && opid >= a.o_N && !bits) bits = KVX_DERR_SRC_PAGE;
@@ -1015,9 +829,9 @@ __device__ __forceinline__ void copy_parts() {
                 const uint32_t pg = lane32(opid, 0);
                 if (pg == ~0u) continue;
                 w.o += (int64_t)pg * a.o_p + (uint64_t)(w.pos - jo0 * a.fd_To.d) * a.o_t * 16;
-                copy_part<OP, MODE, true, HOST, U>(a, w, from_lane);
+                copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
             } else {
-                copy_part<OP, MODE, false, HOST, U>(a, w, from_lane);
+                copy_part<OP, MODE, false, HOST, U>(a, w, me, team * kWave, from_lane);
             }
         }
         at -= total;
@@ -1069,7 +883,7 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
         const uint64_t tokens = (uint64_t)lane64(wave_scan(n), kWave - 1);
         const uint64_t pages = (uint64_t)lane64(wave_scan((uint64_t)g.pages), kWave - 1);
         const uint32_t token_vecs = a.fd_hv.d * a.C;
-        if (!(4 * tokens >= KVX_ORDER_QUARTERS * pages * T && (uint64_t)T * token_vecs >= KVX_ORDER_PIECES * kWave &&
+        if (!(4 * tokens >= KVX_ORDER_QUARTERS * pages * T &&
               tokens * token_vecs * a.fd_L.d >= (uint64_t)W * 8 * KVX_ORDER_TURNS * kWave)) {
             copy_parts<OP, MODE, HOST, U>();
             return;
@@ -1230,9 +1044,9 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
                 for (uint32_t i = 0; i < turns && c.kb < vecs; ++i, c.kb += size * kWave) {
                     c.ke = vecs - c.kb < kWave ? vecs : c.kb + kWave;
                     if (!kPool || (ones >> u & 1)) {
-                        copy_part<OP, MODE, true, HOST, 1>(ca, c, none);
+                        copy_part<OP, MODE, true, HOST, 1>(ca, c, lane, kWave, none);
                     } else {
-                        copy_part<OP, MODE, false, HOST, 1>(ca, c, [&](uint32_t jo, bool valid) {
+                        copy_part<OP, MODE, false, HOST, 1>(ca, c, lane, kWave, [&](uint32_t jo, bool valid) {
                             return valid ? other_page(ca, c.o_off + jo) : ~0u;
                         });
                     }
@@ -1315,18 +1129,40 @@ static int launch_sweep(const Params &p, hipStream_t stream) {
     return hipSuccess;
 }
 
-// The persistent grid's launch when the tokens are runs on both sides.
+// Compute units of the current device, asked for once per device.
+hipError_t device_cus(int *cus) {
+    static std::atomic<int> seen[64];
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 64 && (*cus = seen[dev].load(std::memory_order_relaxed)) > 0) return hipSuccess;
+    const hipError_t q = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (q == hipSuccess && dev < 64) seen[dev].store(*cus, std::memory_order_relaxed);
+    return q;
+}
+
+// The launch of an unplanned call.
 template <int OP>
-static int launch_runs(const Params &p, int cus, hipStream_t stream) {
+static int launch_grid(const Params &p, hipStream_t stream) {
     const Side &t = OP == OP_GATHER ? p.src : p.dst, &o = OP == OP_GATHER ? p.dst : p.src;
+    int cus = 0;
+    const hipError_t e = device_cus(&cus);
+    if (e != hipSuccess) return e;
     const int64_t row = p.row_bytes;
+    const auto adjacent = [&](const Side &x, bool pool) {
+        return !pool || ((p.H == 1 || x.s_h == row) && x.s_t >= (int64_t)p.H * row);
+    };
+    const bool t_adjacent = adjacent(t, true);
+    const SweepMode mode = p.flat ? RUNS : !t_adjacent ? ROWS_H : adjacent(o, OP == OP_TRANSFER) ? TOKENS : ROWS_T;
     typedef void (*GridFn)(GridArgs);
     constexpr int B = KVX_ORDER_BLOCK, U = KVX_PARTS_UNROLL, UL = KVX_LINK_UNROLL;
+#define KVX_MODES(kernel, ...)                                                                                 \
+    {kernel<OP, RUNS, __VA_ARGS__>, kernel<OP, TOKENS, __VA_ARGS__>, kernel<OP, ROWS_T, __VA_ARGS__>,          \
+     kernel<OP, ROWS_H, __VA_ARGS__>}
     static const GridFn order_fns[2] = {kvx_order_kernel<OP, RUNS, B, U>, kvx_order_kernel<OP, TOKENS, B, U>};
-    static const GridFn parts_fns[2] = {kvx_parts_kernel<OP, RUNS, false, U>, kvx_parts_kernel<OP, TOKENS, false, U>};
-    static const GridFn link_fns[2][2] = {
-        {kvx_parts_kernel<OP, RUNS, false, UL>, kvx_parts_kernel<OP, RUNS, true, UL>},
-        {kvx_parts_kernel<OP, TOKENS, false, UL>, kvx_parts_kernel<OP, TOKENS, true, UL>}};
+    static const GridFn parts_fns[4] = KVX_MODES(kvx_parts_kernel, false, U);
+    static const GridFn link_fns[2][4] = {KVX_MODES(kvx_parts_kernel, false, UL), KVX_MODES(kvx_parts_kernel, true, UL)};
+#undef KVX_MODES
     GridArgs a{};
     a.reqs = p.reqs;
     a.err = p.err;
@@ -1355,56 +1191,30 @@ static int launch_runs(const Params &p, int cus, hipStream_t stream) {
     } else {
         a.o_t = p.H * p.vpr;
     }
+    a.t_h = (uint32_t)(t.s_h / 16);
+    a.o_h = OP == OP_TRANSFER ? (uint32_t)(o.s_h / 16) : (uint32_t)p.vpr;
+    a.fd_vpr = p.fd_vpr;
+    a.fd_H = p.fd_H;
     a.fd_Tt = p.fd_Tt;
     a.fd_To = p.fd_To;
     a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
     a.fd_L = make_fastdiv((uint32_t)p.L);
-    const int tokens = p.flat ? 0 : 1;
     const bool link = p.src_host || p.dst_host;
     a.min_part = link ? 0x40000000 : kWave * U;          // over the link whole units
-    if (!link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs) {
-        hipLaunchKernelGGL(order_fns[tokens], dim3((cus + 7) / 8 * 8), dim3(B), 0, stream, a);
+    const int64_t page_vecs = (int64_t)t.T * p.C * p.H * p.vpr;
+    const bool rows = mode == ROWS_T || mode == ROWS_H;
+    const uint64_t small = (uint64_t)cus * KVX_PARTS_BLOCKS_PER_CU * 4 * KVX_TEAM_KIB * kWave;
+    const bool teams = rows && !link && (double)t.pt_len * page_vecs * p.L >= (double)small;
+    a.team_min = teams ? small : ~0ull;
+    if (!rows && !link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs &&
+        page_vecs >= (int64_t)KVX_ORDER_PIECES * kWave) {
+        hipLaunchKernelGGL(order_fns[mode], dim3((cus + 7) / 8 * 8), dim3(B), 0, stream, a);
     } else {
-        const GridFn fn = link ? link_fns[tokens][p.dst_host ? 1 : 0] : parts_fns[tokens];
-        hipLaunchKernelGGL(fn, dim3(cus * (link ? KVX_LINK_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU)), dim3(256), 0,
-                           stream, a);
+        const GridFn fn = link ? link_fns[p.dst_host ? 1 : 0][mode] : parts_fns[mode];
+        const int per_cu = link ? KVX_LINK_BLOCKS_PER_CU : teams ? KVX_TEAM_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU;
+        hipLaunchKernelGGL(fn, dim3(cus * per_cu), dim3(256), 0, stream, a);
     }
     return hipGetLastError();
-}
-
-// The persistent grid's launch when rows are resolved.
-template <int OP>
-static int launch_rows(const Params &p, int cus, hipStream_t stream) {
-    typedef void (*RowsFn)(Params);
-    static const RowsFn fns[2][2] = {{kvx_copy_kernel<OP, false, false>, kvx_copy_kernel<OP, false, true>},
-                                     {kvx_copy_kernel<OP, true, false>, kvx_copy_kernel<OP, true, true>}};
-    const bool tthd = (OP == OP_GATHER ? p.src : p.dst).tok_contig != 0;
-    hipLaunchKernelGGL(fns[tthd][p.dst_host ? 1 : 0], dim3(cus * KVX_ROWS_BLOCKS_PER_CU), dim3(kBlock), 0, stream, p);
-    return hipGetLastError();
-}
-
-// Compute units of the current device, asked for once per device.
-hipError_t device_cus(int *cus) {
-    static std::atomic<int> seen[64];
-    int dev = 0;
-    const hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 64 && (*cus = seen[dev].load(std::memory_order_relaxed)) > 0) return hipSuccess;
-    const hipError_t q = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (q == hipSuccess && dev < 64) seen[dev].store(*cus, std::memory_order_relaxed);
-    return q;
-}
-
-template <int OP>
-static int launch_grid(const Params &p, hipStream_t stream) {
-    const auto adjacent = [&](const Side &x, bool pool) {
-        return !pool || ((p.H == 1 || x.s_h == p.row_bytes) && x.s_t >= (int64_t)p.H * p.row_bytes);
-    };
-    int cus = 0;
-    const hipError_t e = device_cus(&cus);
-    if (e != hipSuccess) return e;
-    if (adjacent(p.src, OP != OP_SCATTER) && adjacent(p.dst, OP != OP_GATHER)) return launch_runs<OP>(p, cus, stream);
-    return launch_rows<OP>(p, cus, stream);
 }
 
 // Sweep when the host chose it (p.sweep), else a persistent grid: as

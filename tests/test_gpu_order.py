@@ -1,7 +1,7 @@
-"""Unplanned calls whose tokens are runs on both sides, bit for bit against
-the oracle: in order (the test build copies every such call in order, the
-product library those of long records) and in parts (the product library's
-way for the rest)."""
+"""Unplanned calls, bit for bit against the oracle: runs on both sides in order
+(the test build copies every such call in order, the product library those of
+long records), rows by teams of wavefronts (the test build all of them, the
+product library those of much data), and the rest in parts."""
 import numpy as np
 import pytest
 
@@ -65,6 +65,39 @@ def test_many_records(library, n_reqs):
     fifth of them empty."""
     spec = [(i % 3, (i * 5) % 4, 0 if i % 5 == 4 else 1 + i % 7, None) for i in range(n_reqs)]
     check(cases.transfer_case("LPCTHD", "LPCTHD", 4, 4, seed=n_reqs, D=8, L=3, H=1, spec=spec))
+
+
+@pytest.mark.parametrize("Ts,Td", [(16, 64), (64, 16), (3, 7), (1, 130)])   # 130: more source pages than lanes
+@pytest.mark.parametrize("H,D,L", [(3, 8, 2), (8, 128, 3), (5, 80, 2)])
+@pytest.mark.parametrize("ls,ld", [("LPCTHD", "LPCHTD"), ("PLCHTD", "LPCTHD"), ("LPCHTD", "PLCHTD")])
+def test_rows(library, ls, ld, H, D, L, Ts, Td):
+    """Head-major sides: odd first slots (half a slot block masked), one token,
+    an empty record, pages left and entered in the middle."""
+    spec = [(1, 3, 1, None), (0, 0, 0, None), (Ts - 1, Td - 1, 2 * Td + 3, None), (0, 1, Ts, None), (2, 0, 3 * Ts + 1, None)]
+    check(cases.transfer_case(ls, ld, Ts, Td, seed=Ts + 3 * Td + H, D=D, L=L, H=H, spec=spec))
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("layout", ["LPCHTD", "PLCHTD"])
+def test_rows_through_a_buffer(library, layout, pinned):
+    check(cases.gather_scatter_case(layout, 24, 2, 80, seed=31, H=5, pinned=pinned))
+
+
+def test_product_library_copies_much_data_of_rows_by_teams():
+    """One record of 4000 tokens over 8 layers, 131 MB, above the size from
+    which the product library's wavefronts share parts; a bad id on each side."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S = PoolSpec(8, 2, 8, 128, T=64, N=70, e=2, layout="PLCHTD")
+    D = PoolSpec(8, 2, 8, 128, T=16, N=270, e=2, layout="LPCTHD")
+    rng = np.random.default_rng(6)
+    src, dst = rng.permutation(70)[:64].astype(np.int32), rng.permutation(270)[:251].astype(np.int32)
+    dst[7] = 270
+    src[11] = -1
+    rows = np.asarray([[0, 0, 0, 5, 3, 4000]], np.int64)
+    check(Workload("case", "long record of rows", {"A": S, "B": D}, [Step("transfer", "A", "B", src, dst, rows)],
+                   value_seed=8, prefill_tag=3))
 
 
 @pytest.mark.parametrize("T,pinned", [(16, False), (64, False), (64, True)])
