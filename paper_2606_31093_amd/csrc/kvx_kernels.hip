@@ -11,14 +11,16 @@
 // The unit of work is one page of the tiling side in one layer; the tiling
 // side is the destination pool for transfer and
 // scatter (each unit then writes one destination page of one layer, and no
-// two units write the same bytes) and the source pool for gather.  Three
+// two units write the same bytes) and the source pool for gather.  Four
 // kernels share the work out:
 // - kvx_sweep_kernel: a planned transfer, one workgroup of one wavefront per
 //   kilobyte of a unit, started in order by the hardware;
 // - kvx_order_kernel: unplanned calls of long records whose tokens are runs
 //   on both sides, a persistent grid that keeps that order;
 // - kvx_parts_kernel: the other unplanned calls (few or short records, rows to
-//   resolve, the host link), a persistent grid over parts of units.
+//   resolve, the host link), a persistent grid over parts of units;
+// - kvx_tile_kernel: unplanned long records between head-major pools, a
+//   persistent grid of workgroups over whole units.
 //
 // Order matters because of the memory, not of the caches: nothing is re-read.
 // A bare copy of random 256 KiB pages moves 6.6 TB/s (read + write) when the
@@ -63,6 +65,9 @@
 // the records in LDS).
 #ifndef KVX_TEAM_KIB
 #define KVX_TEAM_KIB 8
+#endif
+#ifndef KVX_TILE_UNROLL
+#define KVX_TILE_UNROLL 4   // kvx_tile_kernel: vectors in flight per lane
 #endif
 #ifndef KVX_TEAM_PARTS
 #define KVX_TEAM_PARTS 1
@@ -110,6 +115,7 @@
 namespace kvx {
 namespace {
 
+constexpr int kBlock = 256;   // threads that copy a tile
 constexpr int kWave = 64;
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
@@ -178,6 +184,206 @@ __device__ __forceinline__ bool load_req(const Params &p, int32_t r, Req &q) {
     q.j0 = (int32_t)fd_div(p.fd_Tt, (uint32_t)q.t_start);
     q.pages = (int32_t)fd_div(p.fd_Tt, (uint32_t)(q.t_start + q.n - 1)) - q.j0 + 1;
     return true;
+}
+
+// Everything a tile's row loop needs, fixed for the tile.
+struct Tile {
+    char *t_base;         // tiling side at (l, page, c = 0, slot = 0, h = 0)
+    int32_t sa, sb;       // tiling-side slots [sa, sb) of this tile
+    int32_t ntok;         // sb - sa
+    int32_t qo_a;         // other-side position of slot sa
+    int32_t jo0;          // other-side logical page of qo_a
+    int32_t pid;          // this lane's piece page id (-1: invalid / unused)
+    int32_t l;
+};
+
+// Copies a tile's rows: vectors in (c, slot block, h, slot, v) order over the
+// blocks of KVX_SLOT_BLOCK slots that meet [sa, sb), with the slots outside
+// masked.
+template <int U>
+__device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const Tile &t) {
+    const Side &ts = p.dst, &os = p.src;
+    const uint32_t H = p.H, vpr = p.vpr;
+    // A head-major tiling side takes its vectors in (c, slot block, h, slot,
+    // v) order over the blocks of SB slots that meet [sa, sb): the tiling
+    // side's writes are SB-row runs, and the other side's reads, whose
+    // consecutive heads are adjacent, fill whole slots within a few passes.
+    // (Page order, one head at a time, left the reads 256-byte pieces a
+    // kilobyte apart: 11% slower on a 16-token -> 64-token relayout.)
+    constexpr uint32_t SB = KVX_SLOT_BLOCK;
+    const uint32_t blk0 = (uint32_t)t.sa / SB, nblk = ((uint32_t)t.sb - 1) / SB - blk0 + 1;
+    const uint32_t rows_c = H * nblk * SB;
+    const uint32_t total = rows_c * vpr * (uint32_t)p.C;
+    const char *o_l = os.base + (int64_t)t.l * os.s_l;
+    // The trip count is the same for every lane: the page-id broadcast below
+    // reads other lanes, which must all still be active.
+    for (uint32_t kb = 0; kb < total; kb += kBlock * U) {
+        const char *src[U];
+        char *dst[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t kk = kb + threadIdx.x + u * kBlock;
+            const uint32_t k = kk < total ? kk : total - 1;
+            bool valid = kk < total;
+            const uint32_t rw = fd_div(p.fd_vpr, k);
+            const uint32_t v = k - rw * vpr;
+            const uint32_t c = rw >= rows_c;
+            const uint32_t rr = rw - c * rows_c;
+            const uint32_t q1 = rr / SB;
+            const uint32_t blk = fd_div(p.fd_H, q1);
+            const uint32_t h = q1 - blk * H;
+            const uint32_t slot = (blk0 + blk) * SB + (rr - q1 * SB);
+            valid = valid && slot >= (uint32_t)t.sa && slot < (uint32_t)t.sb;
+            const int32_t tt = (int32_t)slot - t.sa;  // token index within the tile
+            char *ta = t.t_base + c * ts.s_c + (int64_t)slot * ts.s_t + (int64_t)h * ts.s_h + v * 16;
+            const uint32_t qo = (uint32_t)(t.qo_a + tt);
+            const uint32_t jo = fd_div(p.fd_To, qo);
+            const uint32_t so = qo - jo * (uint32_t)os.T;
+            const uint32_t piece = jo - (uint32_t)t.jo0;
+            int32_t pg = __shfl(t.pid, piece < kWave ? piece : kWave - 1, kWave);
+            if (valid && piece >= kWave) {
+                // More pieces than lanes: resolve this row's page directly.
+                const int64_t idx = q.o_pt_off + jo;
+                pg = -1;
+                if (idx < 0 || idx >= os.pt_len) {
+                    report(p, KVX_DERR_PT_RANGE);
+                } else {
+                    const int32_t id = os.pt[idx];
+                    if (id < 0 || id >= os.N) report(p, KVX_DERR_SRC_PAGE);
+                    else pg = id;
+                }
+            }
+            valid = valid && pg >= 0;
+            const char *oa = o_l + (int64_t)pg * os.s_p + c * os.s_c + (int64_t)so * os.s_t +
+                             (int64_t)h * os.s_h + v * 16;
+            ok[u] = valid;
+            src[u] = oa;
+            dst[u] = ta;
+        }
+        v4u val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) val[u] = ld16(src[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) st16<false>(dst[u], val[u]);
+    }
+}
+
+// Tile (request q, its tiling-side page jj, layer l), U vectors per thread in
+// flight.
+template <int U>
+__device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t jj, int32_t layer) {
+    const Side &ts = p.dst, &os = p.src;
+
+    Tile t;
+    t.l = layer;
+    const int64_t j = q.j0 + jj;
+    const int64_t page_lo = j * ts.T;
+    const int64_t qa = page_lo > q.t_start ? page_lo : q.t_start;
+    const int64_t q_end = (int64_t)q.t_start + q.n;
+    const int64_t qb = page_lo + ts.T < q_end ? page_lo + ts.T : q_end;
+    t.sa = (int32_t)(qa - page_lo);
+    t.sb = (int32_t)(qb - page_lo);
+    t.ntok = t.sb - t.sa;
+
+    // Tiling-side page (one per tile; a uniform load).
+    const int64_t tidx = q.t_pt_off + j;
+    if (tidx < 0 || tidx >= ts.pt_len) {
+        if (threadIdx.x == 0) report(p, KVX_DERR_PT_RANGE);
+        return;
+    }
+    const int32_t tpage = ts.pt[tidx];
+    if (tpage < 0 || tpage >= ts.N) {
+        if (threadIdx.x == 0) report(p, KVX_DERR_DST_PAGE);
+        return;
+    }
+    t.t_base = ts.base + (int64_t)t.l * ts.s_l + (int64_t)tpage * ts.s_p;
+
+    const int32_t delta = q.o_start - q.t_start;
+    t.qo_a = (int32_t)qa + delta;
+    t.jo0 = (int32_t)fd_div(p.fd_To, (uint32_t)t.qo_a);
+    const int32_t jo1 = (int32_t)fd_div(p.fd_To, (uint32_t)((int32_t)qb - 1 + delta));
+    const int32_t K = jo1 - t.jo0 + 1;
+    const int32_t lane = threadIdx.x & (kWave - 1);
+    t.pid = -1;
+    if (lane < K) {
+        const int64_t idx = q.o_pt_off + t.jo0 + lane;
+        uint32_t bad = 0;
+        if (idx < 0 || idx >= os.pt_len) {
+            bad = KVX_DERR_PT_RANGE;
+        } else {
+            const int32_t id = os.pt[idx];
+            if (id < 0 || id >= os.N) bad = KVX_DERR_SRC_PAGE;
+            else t.pid = id;
+        }
+        if (bad && threadIdx.x < kWave) report(p, bad);   // the first wavefront
+    }
+    copy_rows<U>(p, q, t);
+}
+
+// Inclusive sum of x over the workgroup's threads (x = 0 past the chunk).
+// Every thread of the workgroup must call it: it contains barriers.
+__device__ __forceinline__ int64_t block_scan(int64_t x, int64_t *s_wave) {
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int64_t y = __shfl_up(x, d, kWave);
+        if (lane >= d) x += y;
+    }
+    if (lane == kWave - 1) s_wave[wid] = x;
+    __syncthreads();
+    for (int w = 0; w < wid; ++w) x += s_wave[w];
+    return x;
+}
+
+// Long records between head-major pools: a workgroup per page of a layer.  Of the
+// unplanned ways it is the fastest here (5.2 GB of 256 KiB pages: 876 us; teams
+// of the parts kernel 911, in order 953) although teams walk through the pages
+// alike; everywhere else that rows are resolved it ties or loses (200 tokens
+// 31 us against 17, 8.1 GB head-major to token-major 1545 against 1511).
+__global__ void __launch_bounds__(kBlock) kvx_tile_kernel(Params p) {
+    // Records are taken kBlock at a time: each thread reads one and counts
+    // its tiles, a workgroup scan turns the counts into tile ranges, and the
+    // workgroup's tiles inside the chunk find their record by binary search.
+    __shared__ int64_t s_end[kBlock];   // end (exclusive) of record i's tiles in the chunk
+    __shared__ int64_t s_wave[kBlock / kWave];
+    Req q;
+    int32_t cached = -1;
+    const int64_t stride = (int64_t)gridDim.x;
+    int64_t tile = blockIdx.x, chunk_base = 0;
+    for (int32_t r0 = 0; r0 < p.n_reqs; r0 += kBlock) {
+        const int32_t nr = p.n_reqs - r0 < kBlock ? p.n_reqs - r0 : kBlock;
+        int64_t cnt = 0;
+        if ((int32_t)threadIdx.x < nr) {
+            Req mine;
+            if (!load_req(p, r0 + threadIdx.x, mine) && blockIdx.x == 0)
+                report(p, KVX_DERR_BAD_REQ);
+            cnt = mine.pages * p.L;
+        }
+        s_end[threadIdx.x] = block_scan(cnt, s_wave);
+        __syncthreads();
+        const int64_t chunk_tiles = s_end[kBlock - 1];
+        for (; tile < chunk_base + chunk_tiles; tile += stride) {   // uniform
+            const int64_t local = tile - chunk_base;
+            int32_t lo = 0, hi = nr - 1;             // first record whose range ends past `local`
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (s_end[mid] > local) hi = mid;
+                else lo = mid + 1;
+            }
+            if (r0 + lo != cached) {
+                load_req(p, r0 + lo, q);
+                cached = r0 + lo;
+            }
+            const int64_t in_rec = local - (lo ? s_end[lo - 1] : 0);
+            const int64_t jj = in_rec / p.L;
+            do_tile<KVX_TILE_UNROLL>(p, q, jj, (int32_t)(in_rec - jj * p.L));
+        }
+        chunk_base += chunk_tiles;
+        __syncthreads();                             // s_end and s_wave are rewritten next chunk
+    }
 }
 
 // Lane k's row of a sweep piece: kv component c, slot, head h, vector v of
@@ -1206,6 +1412,11 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     const uint64_t small = (uint64_t)cus * KVX_PARTS_BLOCKS_PER_CU * 4 * KVX_TEAM_KIB * kWave;
     const bool teams = rows && !link && (double)t.pt_len * page_vecs * p.L >= (double)small;
     a.team_min = teams ? small : ~0ull;
+    if (OP == OP_TRANSFER && teams && mode == ROWS_H && !adjacent(o, true) &&
+        t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs) {
+        hipLaunchKernelGGL(kvx_tile_kernel, dim3(cus * KVX_TEAM_BLOCKS_PER_CU), dim3(kBlock), 0, stream, p);
+        return hipGetLastError();
+    }
     if (!rows && !link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs &&
         page_vecs >= (int64_t)KVX_ORDER_PIECES * kWave) {
         hipLaunchKernelGGL(order_fns[mode], dim3((cus + 7) / 8 * 8), dim3(B), 0, stream, a);
