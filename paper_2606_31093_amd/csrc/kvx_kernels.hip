@@ -869,7 +869,11 @@ __device__ __forceinline__ bool part_vector(const GridArgs &a, const GridPart &g
 }
 
 // Copies a part, U vectors per lane in flight: thread `me` of the `span` that
-// share it.
+// share it.  Lanes without a vector load one all the same, that of the part's
+// last or the source's first: between loads that some lanes skip the compiler
+// waits for all that is in flight, which left one or two of the U (200 tokens of
+// 36 x 8 x 128 with a padded table 18.8 us so, 15.5 with all four in flight;
+// gathered from 16 records of 1 to 20 tokens and scattered 35.5 and 30.2).
 template <int OP, SweepMode MODE, bool ONE, bool HOST, int U, class PageOf>
 __device__ __forceinline__ void copy_part(const GridArgs &a, const GridPart &g, uint32_t me, uint32_t span,
                                           PageOf page_of) {
@@ -883,7 +887,7 @@ __device__ __forceinline__ void copy_part(const GridArgs &a, const GridPart &g, 
             have[u] = part_vector<OP, MODE, ONE>(a, g, k0 + u * span + me, page_of, src[u], dst[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (have[u]) val[u] = ld16(src[u]);
+            val[u] = ld16(have[u] || (ONE && MODE != ROWS_H) ? src[u] : OP == OP_GATHER ? a.t_base : a.o_base);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (have[u]) st16<HOST>(dst[u], val[u]);

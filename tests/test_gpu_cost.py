@@ -1,0 +1,76 @@
+"""Calls that must not cost more than others of the same data.  Each pair is
+timed in turn on the same pools, and the least times are compared: the bounds
+lie between what the call takes and what it took when it was at fault."""
+import numpy as np
+import pytest
+
+from paper_2606_31093_amd import workloads as W
+from paper_2606_31093_amd.workloads import BufSpec, PoolSpec
+
+pytestmark = pytest.mark.gpu
+TOKEN, HEAD = "LPCTHD", "PLCHTD"
+
+
+@pytest.fixture
+def kvx():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_31093_amd import kvx
+    kvx.lib()
+    return kvx
+
+
+def least(*calls, rounds=9, reps=20):
+    """Least time of each call, in us: the calls take turns."""
+    import torch
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = [float("inf")] * len(calls)
+    for k in range(rounds):
+        for i, call in enumerate(calls):
+            a.record()
+            for _ in range(reps if k else 3):
+                call()
+            b.record()
+            b.synchronize()
+            if k:
+                best[i] = min(best[i], a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
+class Pools:
+    """Two pools and tables of `per` pages for each of n records."""
+
+    def __init__(self, kvx, src, dst, n, per):
+        self.kvx, self.src, self.dst = kvx, src, dst
+        self.mem = [W.alloc_side(s, "cuda").zero_() for s in (src, dst)]
+        rng = np.random.default_rng(n)
+        self.tables = [rng.permutation(s.N)[:n * per].astype(np.int32) for s in (src, dst)]
+        self.n, self.per = n, per
+
+    def rows(self, tokens, src_start=0, dst_start=0):
+        r = np.arange(self.n) * self.per
+        one = np.ones(self.n, np.int64)
+        return np.stack([r, r, 0 * r, one * src_start, one * dst_start, one * tokens], axis=1)
+
+    def transfer(self, rows, pad=0):
+        k = self.kvx
+        pt = [k.device_table(np.concatenate([t, np.zeros(pad, np.int32)]), "cuda") for t in self.tables]
+        reqs = k.device_reqs(rows, "cuda")
+        return lambda: k.kvx_transfer(self.mem[0], self.src, self.mem[1], self.dst, pt[0], pt[1], reqs)
+
+
+def check(got, bound, what):
+    assert got <= bound, f"{what}: {got:.2f} of the other's time, bound {bound}"
+
+
+@pytest.mark.parametrize("n,tokens", [(64, 3), (1, 200)])
+@pytest.mark.parametrize("ls,ld", [(TOKEN, TOKEN)])
+def test_table_longer_than_the_records_need(kvx, ls, ld, n, tokens):
+    """A padded table must not take a short call to a way made for long ones
+    (at fault 1.25 to 1.8; 1.0 to 1.15)."""
+    S, D = (PoolSpec(36, 2, 8, 128, T=64, N=256, e=2, layout=x) for x in (ls, ld))
+    p = Pools(kvx, S, D, n, 4 if n == 1 else 1)
+    rows = p.rows(tokens)
+    padded, exact = least(p.transfer(rows, pad=64 * 64), p.transfer(rows))
+    check(padded / exact, 1.22, f"{n} x {tokens} tokens {ls} -> {ld}, padded table")
