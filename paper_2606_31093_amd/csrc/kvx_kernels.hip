@@ -50,6 +50,17 @@
 #ifndef KVX_PARTS_UNROLL
 #define KVX_PARTS_UNROLL 4
 #endif
+// The same for more than 64 records: threads per workgroup, which share their
+// look at the records, and workgroups per CU.
+#ifndef KVX_SHARE_BLOCK
+#define KVX_SHARE_BLOCK 512
+#endif
+#ifndef KVX_SHARE_BLOCKS_PER_CU
+#define KVX_SHARE_BLOCKS_PER_CU 3
+#endif
+#ifndef KVX_SHARE_TEAM_BLOCKS_PER_CU
+#define KVX_SHARE_TEAM_BLOCKS_PER_CU 2
+#endif
 // Parts per wavefront that units are cut into.  64 half-filled pages of 36
 // layers: 108 us with 32, 116 with 8.
 #ifndef KVX_GRID_PARTS
@@ -692,6 +703,8 @@ struct GridArgs {
     FastDiv fd_vpr, fd_H;             // rows only
     uint32_t min_part;                // vectors a part has at least
     uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part
+    float even, team_even;            // part size aimed at, in 64 U (256 U for teams) vectors, for each 64 vectors
+                                      // of a wavefront's 64 records
 };
 
 // A record as the grid sees it: the part of it whose tiling-side pages the
@@ -757,6 +770,18 @@ __device__ __forceinline__ uint64_t wave_scan(uint64_t x) {
     KVX_DPP_ADD(0x118, 0xf)
     KVX_DPP_ADD(0x142, 0xa)   // row_bcast 15 into rows 1 and 3
     KVX_DPP_ADD(0x143, 0xc)   // row_bcast 31 into rows 2 and 3
+#undef KVX_DPP_ADD
+    return x;
+}
+
+__device__ __forceinline__ uint32_t wave_scan32(uint32_t x) {
+#define KVX_DPP_ADD(ctrl, rows) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false);
+    KVX_DPP_ADD(0x111, 0xf)   // the same steps
+    KVX_DPP_ADD(0x112, 0xf)
+    KVX_DPP_ADD(0x114, 0xf)
+    KVX_DPP_ADD(0x118, 0xf)
+    KVX_DPP_ADD(0x142, 0xa)
+    KVX_DPP_ADD(0x143, 0xc)
 #undef KVX_DPP_ADD
     return x;
 }
@@ -919,53 +944,100 @@ __device__ __forceinline__ const GridArgs &fresh_args() {
     return *(const GridArgs *)ap;
 }
 
+// The records of a workgroup of B threads that share their look at them.
+template <int B>
+struct Records {
+    GridRec rec[B];
+    int64_t end[B];              // parts up to and with record i's, among its 64
+    uint32_t parts[B];           // parts of each of record i's pages
+    uint32_t part_vecs[B / kWave];
+};
+
 // Persistent grid over parts of units, for calls of few or short records and
 // for those that resolve rows.
-// Every wavefront looks at the records by itself, 64 at a time, one per lane:
-// a scan over the lanes turns their parts into ranges, and the record of a
-// part is found with one ballot and read with lane reads, so nothing waits
-// for a barrier or LDS.  What bounds a small call is that chain of dependent
+// Every wavefront looks at 64 records, one per lane: a scan over the lanes
+// turns their parts into ranges, and the record of a part is found with one
+// ballot and read with lane reads.  A call of up to 64 records needs no LDS
+// and no barrier: every wavefront looks at all of them.  Of more, each
+// wavefront of a workgroup looks at another 64 and leaves what it found in
+// LDS: looking at 64 records costs a wavefront about 0.5 us whether or not
+// any of their parts are its own (16384 records of 1-4 tokens of 2 x 2 x 64:
+// 533 us when every wavefront looked at all of them, 100 so).
+// What bounds a small call is the chain of dependent
 // loads (records, page ids of both sides at once, data) and the width of the
 // chip: a unit is cut into parts of 64 U vectors, or larger ones once there
 // are KVX_GRID_PARTS per wavefront.  Layers are innermost, so that the parts
 // in flight spread over the pool.  Against whole units per wavefront and
-// records in LDS (us, start -> now): 64 decode records 14.8 -> 12.9, 64
+// records in LDS (us, that -> this): 64 decode records 14.8 -> 12.9, 64
 // half-filled pages 145 -> 108, 4 x 200 tokens 60.2 -> 48.4, 1024 decode
 // records 167.6 -> 163.6; 16384 of them 2331 -> 2340 (equal).
-template <int OP, SweepMode MODE, bool HOST, int U>
-__device__ __forceinline__ void copy_parts() {
-    constexpr bool kPool = OP == OP_TRANSFER;
+template <int OP, SweepMode MODE, bool HOST, int U, int B, bool SHARE>
+__device__ __forceinline__ void copy_parts(Records<B> *shared) {
+    constexpr bool kPool = OP == OP_TRANSFER, kRows = MODE == ROWS_T || MODE == ROWS_H;
     constexpr uint32_t kUnit = kWave * U, kTeam = 4;
-    const uint32_t lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t workers = gridDim.x * waves;
-    uint32_t team = 1, me = lane;
-    int64_t at = (int64_t)blockIdx.x * waves + wave;
+    constexpr int kWaves = B / kWave, kStep = SHARE ? B : kWave;
+    const uint32_t lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t workers = gridDim.x * kWaves;
     const int32_t n_reqs = fresh_args().n_reqs;
-    kvx_req raw = load_raw(fresh_args(), lane);
-    for (int32_t r0 = 0; r0 < n_reqs; r0 += kWave) {
-        const GridArgs &ra = fresh_args();
-        const uint32_t L = ra.fd_L.d, T = ra.fd_Tt.d;
-        GridRec g;                                         // (a lane without a record has an empty one)
-        const uint32_t bad = grid_record<OP>(ra, raw, g);
-        if (bad && blockIdx.x == 0 && threadIdx.x < kWave && ra.err) atomicOr(ra.err, bad);
-        raw = load_raw(ra, r0 + kWave + lane);             // the next 64, on their way meanwhile
-        // vectors of the record's largest page, and of all records' pages
-        const uint32_t tile = record_slots<MODE>(g, T) * ra.fd_hv.d * ra.C;
-        const uint64_t all = (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * L *
-                             (uint32_t)((n_reqs + kWave - 1) / kWave);
-        if (r0 == 0 && (MODE == ROWS_T || MODE == ROWS_H) && all >= ra.team_min) {
+    uint32_t team = 1, me = lane;
+    int64_t at = (int64_t)blockIdx.x * kWaves + wave;
+    if (SHARE && kRows) {
+        const GridArgs &a = fresh_args();
+        GridRec g;
+        (void)grid_record<OP>(a, load_raw(a, lane), g);
+        const uint64_t v = (uint64_t)g.pages * (record_slots<MODE>(g, a.fd_Tt.d) * a.fd_hv.d * a.C);
+        const uint64_t all = (uint64_t)lane64(wave_scan(v), kWave - 1) * a.fd_L.d * (uint32_t)((n_reqs + kWave - 1) / kWave);
+        if (all >= a.team_min) {
             team = kTeam;
             me = threadIdx.x % (kTeam * kWave);
             at /= kTeam;
         }
+    }
+    for (int32_t r0 = 0; r0 < (SHARE ? n_reqs : 1); r0 += kStep) {
+        const GridArgs &ra = fresh_args();
+        const uint32_t L = ra.fd_L.d, T = ra.fd_Tt.d;
+        GridRec g;                                         // (a lane without a record has an empty one)
+        const uint32_t bad = grid_record<OP>(ra, load_raw(ra, r0 + (SHARE ? threadIdx.x : lane)), g);
+        if (bad && blockIdx.x == 0 && (SHARE || wave == 0) && ra.err) atomicOr(ra.err, bad);
+        const uint32_t tile = record_slots<MODE>(g, T) * ra.fd_hv.d * ra.C;   // vectors of the record's largest page
+        if (!SHARE && kRows && (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * L >= ra.team_min) {
+            team = kTeam;
+            me = threadIdx.x % (kTeam * kWave);
+            at /= kTeam;
+        }
+        // the vectors (in 64s) of these 64 records' pages
+        const uint64_t v = (uint64_t)g.pages * ((tile + kWave - 1) / kWave);
+        const uint32_t most = 1u << 25, all = lane32(wave_scan32(v < most ? (uint32_t)v : most), kWave - 1);
         // a part: 64 U vectors, or more when there are many
-        const uint64_t even = all / ((uint64_t)workers * (team == 1 ? KVX_GRID_PARTS : KVX_TEAM_PARTS));
-        const uint32_t fit = even > 0x3fffffff ? 0x40000000 : (uint32_t)(even / (kUnit * team) + 1) * kUnit * team;
-        const uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
-        const uint32_t parts = (tile + part_vecs - 1) / part_vecs;
-        const uint64_t end = wave_scan((uint64_t)g.pages * parts);
-        const int64_t total = lane64(end, kWave - 1) * L;
+        const uint32_t unit = kUnit * team;
+        const float even = (float)all * (team == 1 ? ra.even : ra.team_even);
+        const uint32_t fit = (even < (float)(0x40000000 / unit) ? (uint32_t)even + 1 : 0x40000000 / unit) * unit;
+        uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
+        uint32_t parts = (tile + part_vecs - 1) / part_vecs;
+        const uint64_t count = (uint64_t)g.pages * parts;
+        int64_t end = __ballot(count >> 25) == 0 ? (int64_t)wave_scan32((uint32_t)count) : (int64_t)wave_scan(count);
+        int64_t ends = 0;                                  // lane i: parts of wavefront i's records
+        if (SHARE) {
+            shared->rec[threadIdx.x] = g;
+            shared->end[threadIdx.x] = end;
+            shared->parts[threadIdx.x] = parts;
+            if (lane == 0) shared->part_vecs[wave] = part_vecs;
+            __syncthreads();
+            if (lane < (uint32_t)kWaves) ends = shared->end[lane * kWave + kWave - 1];
+        }
+        for (int c = 0; c < (SHARE ? kWaves : 1); ++c) {
+        const int64_t total = (SHARE ? lane64(ends, c) : lane64(end, kWave - 1)) * L;
+        if (SHARE) {
+            if (at >= total) {
+                at -= total;
+                continue;
+            }
+            g = shared->rec[c * kWave + lane];
+            end = shared->end[c * kWave + lane];
+            parts = shared->parts[c * kWave + lane];
+            part_vecs = __builtin_amdgcn_readfirstlane(shared->part_vecs[c]);
+        }
         for (; at < total; at += workers / team) {
             const GridArgs &a = fresh_args();
             const uint64_t rem = at < INT32_MAX ? fd_div(a.fd_L, (uint32_t)at) : (uint64_t)at / L;
@@ -1045,12 +1117,21 @@ __device__ __forceinline__ void copy_parts() {
             }
         }
         at -= total;
+        }
+        if (SHARE) __syncthreads();                         // the next records take the place of these
     }
 }
 
 template <int OP, SweepMode MODE, bool HOST, int U>
-__global__ void __launch_bounds__(256) kvx_parts_kernel(GridArgs) {
-    copy_parts<OP, MODE, HOST, U>();
+__global__ void __launch_bounds__(kBlock) kvx_parts_kernel(GridArgs) {
+    copy_parts<OP, MODE, HOST, U, kBlock, false>(nullptr);
+}
+
+// The same for more than 64 records.
+template <int OP, SweepMode MODE, bool HOST, int U>
+__global__ void __launch_bounds__(KVX_SHARE_BLOCK) kvx_shared_parts_kernel(GridArgs) {
+    __shared__ Records<KVX_SHARE_BLOCK> shared;
+    copy_parts<OP, MODE, HOST, U, KVX_SHARE_BLOCK, true>(&shared);
 }
 
 // Persistent grid that keeps the sweep's order, for calls of long records.
@@ -1076,8 +1157,9 @@ template <int OP, SweepMode MODE, int B, int U>
 __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
     constexpr bool HOST = false;                   // (never over the link)
     constexpr bool kPool = OP == OP_TRANSFER;
-    __shared__ int64_t s_end[B];                   // end of record i's pages among the chunk's
-    __shared__ GridRec s_rec[B];
+    __shared__ Records<B> shared;
+    int64_t *const s_end = shared.end;             // end of record i's pages among the chunk's
+    GridRec *const s_rec = shared.rec;
     __shared__ int64_t s_sum[B / kWave];
     __shared__ uint32_t s_max[B / kWave];
     const uint32_t lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1095,7 +1177,8 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
         const uint32_t token_vecs = a.fd_hv.d * a.C;
         if (!(4 * tokens >= KVX_ORDER_QUARTERS * pages * T &&
               tokens * token_vecs * a.fd_L.d >= (uint64_t)W * 8 * KVX_ORDER_TURNS * kWave)) {
-            copy_parts<OP, MODE, HOST, U>();
+            if (n_reqs > kWave) copy_parts<OP, MODE, HOST, U, B, true>(&shared);
+            else copy_parts<OP, MODE, HOST, U, B, false>(nullptr);
             return;
         }
     }
@@ -1370,8 +1453,12 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     {kernel<OP, RUNS, __VA_ARGS__>, kernel<OP, TOKENS, __VA_ARGS__>, kernel<OP, ROWS_T, __VA_ARGS__>,          \
      kernel<OP, ROWS_H, __VA_ARGS__>}
     static const GridFn order_fns[2] = {kvx_order_kernel<OP, RUNS, B, U>, kvx_order_kernel<OP, TOKENS, B, U>};
-    static const GridFn parts_fns[4] = KVX_MODES(kvx_parts_kernel, false, U);
-    static const GridFn link_fns[2][4] = {KVX_MODES(kvx_parts_kernel, false, UL), KVX_MODES(kvx_parts_kernel, true, UL)};
+    // [more than 64 records][mode], and over the link [into host memory] of those
+    static const GridFn parts_fns[2][4] = {KVX_MODES(kvx_parts_kernel, false, U),
+                                           KVX_MODES(kvx_shared_parts_kernel, false, U)};
+    static const GridFn link_fns[2][2][4] = {
+        {KVX_MODES(kvx_parts_kernel, false, UL), KVX_MODES(kvx_shared_parts_kernel, false, UL)},
+        {KVX_MODES(kvx_parts_kernel, true, UL), KVX_MODES(kvx_shared_parts_kernel, true, UL)}};
 #undef KVX_MODES
     GridArgs a{};
     a.reqs = p.reqs;
@@ -1421,14 +1508,20 @@ static int launch_grid(const Params &p, hipStream_t stream) {
         hipLaunchKernelGGL(kvx_tile_kernel, dim3(cus * KVX_TEAM_BLOCKS_PER_CU), dim3(kBlock), 0, stream, p);
         return hipGetLastError();
     }
-    if (!rows && !link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs &&
-        page_vecs >= (int64_t)KVX_ORDER_PIECES * kWave) {
-        hipLaunchKernelGGL(order_fns[mode], dim3((cus + 7) / 8 * 8), dim3(B), 0, stream, a);
-    } else {
-        const GridFn fn = link ? link_fns[p.dst_host ? 1 : 0][mode] : parts_fns[mode];
-        const int per_cu = link ? KVX_LINK_BLOCKS_PER_CU : teams ? KVX_TEAM_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU;
-        hipLaunchKernelGGL(fn, dim3(cus * per_cu), dim3(256), 0, stream, a);
-    }
+    const bool order = !rows && !link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs &&
+                       page_vecs >= (int64_t)KVX_ORDER_PIECES * kWave;
+    const bool share = p.n_reqs > kWave;
+    const int threads = order ? B : share ? KVX_SHARE_BLOCK : kBlock;
+    int blocks = (cus + 7) / 8 * 8;
+    if (!order && link) blocks = cus * KVX_LINK_BLOCKS_PER_CU * kBlock / threads;
+    else if (!order && teams) blocks = cus * (share ? KVX_SHARE_TEAM_BLOCKS_PER_CU : KVX_TEAM_BLOCKS_PER_CU);
+    else if (!order) blocks = cus * (share ? KVX_SHARE_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU);
+    // the vectors of all records, were they like these 64, over the parts aimed at
+    const float per_64 = 64.f * p.L * ((p.n_reqs + kWave - 1) / kWave), waves = (float)blocks * (threads / kWave);
+    a.even = per_64 / (waves * KVX_GRID_PARTS * kWave * (link ? UL : U));
+    a.team_even = per_64 / (waves * KVX_TEAM_PARTS * kWave * 4 * U);
+    const GridFn fn = order ? order_fns[mode] : link ? link_fns[p.dst_host ? 1 : 0][share][mode] : parts_fns[share][mode];
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -74,3 +74,15 @@ def test_table_longer_than_the_records_need(kvx, ls, ld, n, tokens):
     rows = p.rows(tokens)
     padded, exact = least(p.transfer(rows, pad=64 * 64), p.transfer(rows))
     check(padded / exact, 1.22, f"{n} x {tokens} tokens {ls} -> {ld}, padded table")
+
+
+def test_many_short_records(kvx):
+    """16384 records of 2 tokens against 256 of 128 tokens, of a small model
+    (at fault 30; 6)."""
+    S = PoolSpec(2, 2, 2, 64, T=64, N=1024, e=2, layout=TOKEN)
+    p = Pools(kvx, S, S, 256, 2)
+    few = p.transfer(p.rows(128))
+    r = np.arange(16384)
+    many = np.stack([r // 32, r // 32, 0 * r, r % 32 * 2, r % 32 * 2, 0 * r + 2], axis=1)
+    many, few = least(p.transfer(many), few)
+    check(many / few, 14, "16384 short records")

@@ -67,6 +67,38 @@ def test_many_records(library, n_reqs):
     check(cases.transfer_case("LPCTHD", "LPCTHD", 4, 4, seed=n_reqs, D=8, L=3, H=1, spec=spec))
 
 
+@pytest.mark.parametrize("n_reqs", [64, 65, 511, 512, 513, 1100])
+@pytest.mark.parametrize("ls,ld", [("LPCTHD", "PLCHTD"), ("PLCHTD", "LPCTHD"), ("LPCHTD", "PLCHTD")])
+def test_many_records_of_rows(library, ls, ld, n_reqs):
+    """The same around the records that a workgroup shares its look at: every
+    seventh record is empty, some begin in the middle of a page or span two."""
+    spec = [(i % 3, (i * 5) % 4, 0 if i % 7 == 4 else 1 + i % 6, None) for i in range(n_reqs)]
+    check(cases.transfer_case(ls, ld, 4, 4, seed=n_reqs, D=8, L=3, H=3, spec=spec))
+
+
+@pytest.mark.parametrize("layout", ["LPCTHD", "PLCHTD"])
+@pytest.mark.parametrize("n_reqs,pinned", [(65, False), (600, False), (600, True)])
+def test_many_records_through_a_buffer(library, layout, n_reqs, pinned):
+    """Gathered and scattered; the last record's block does not fit the buffer."""
+    rng = np.random.default_rng(n_reqs)
+    n = rng.integers(0, 9, size=n_reqs)
+    S = PoolSpec(2, 2, 2, 8, T=4, N=2 * n_reqs + 8, e=2, layout=layout)
+    block = 2 * 2 * n * 2 * 8
+    off = np.concatenate([[0], np.cumsum(block)[:-1]])
+    n[-1] = 9
+    buf = BufSpec(2, 2, 2, 8, 2, cap=int(block.sum()))
+    r = np.arange(n_reqs)
+    start = rng.integers(0, 4, size=n_reqs) * (n < 5)
+    src, dst = (rng.permutation(S.N)[:3 * n_reqs].astype(np.int32) for _ in range(2))
+    src[5], dst[9] = S.N, -1
+    gather = np.stack([2 * r, 0 * r, off, start, 0 * r, np.minimum(n, 8 - start)], axis=1)
+    scatter = np.stack([0 * r, 2 * r, off, 0 * r, start, np.minimum(n, 8 - start)], axis=1)
+    gather[-1, 5] = scatter[-1, 5] = 9
+    check(Workload("case", "many records through a buffer", {"A": S, "buf": buf, "B": S},
+                   [Step("gather", "A", "buf", src, None, gather), Step("scatter", "buf", "B", None, dst, scatter)],
+                   host_sides=("buf",) if pinned else (), value_seed=9, prefill_tag=4))
+
+
 @pytest.mark.parametrize("Ts,Td", [(16, 64), (64, 16), (3, 7), (1, 130)])   # 130: more source pages than lanes
 @pytest.mark.parametrize("H,D,L", [(3, 8, 2), (8, 128, 3), (5, 80, 2)])
 @pytest.mark.parametrize("ls,ld", [("LPCTHD", "LPCHTD"), ("PLCHTD", "LPCTHD"), ("LPCHTD", "PLCHTD")])
