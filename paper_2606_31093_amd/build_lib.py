@@ -25,7 +25,7 @@ LIBRARY = os.path.join(PKG, "libkvx.so")
 TEST_LIBRARY = os.path.join(PKG, "libkvx_test.so")
 TEST_DEFINES = ("KVX_HASH_IDLE_POLLS=1", "KVX_SWEEP_MIN_BYTES=0", "KVX_SWEEP_MAX_BLOCKS=2048",
                 "KVX_LAUNCH_CHOICE_DEFAULT=1", "KVX_ORDER_PAGES=0", "KVX_ORDER_PIECES=0",
-                "KVX_ORDER_QUARTERS=0", "KVX_ORDER_TURNS=0", "KVX_TEAM_KIB=0")
+                "KVX_ORDER_QUARTERS=0", "KVX_ORDER_TURNS=0", "KVX_TEAM_KIB=0", "KVX_TEAM_UNIT=0")
 SOURCES = [os.path.join(CSRC, "kvx_kernels.hip"), os.path.join(CSRC, "kvx_hash.hip"),
            os.path.join(CSRC, "kvx_api.cpp")]
 HEADERS = [os.path.join(INCLUDE, "kvx.h"), os.path.join(CSRC, "kvx_internal.h"),

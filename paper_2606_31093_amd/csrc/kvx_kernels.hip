@@ -11,16 +11,15 @@
 // The unit of work is one page of the tiling side in one layer; the tiling
 // side is the destination pool for transfer and
 // scatter (each unit then writes one destination page of one layer, and no
-// two units write the same bytes) and the source pool for gather.  Four
+// two units write the same bytes) and the source pool for gather.  Three
 // kernels share the work out:
 // - kvx_sweep_kernel: a planned transfer, one workgroup of one wavefront per
 //   kilobyte of a unit, started in order by the hardware;
 // - kvx_order_kernel: unplanned calls of long records whose tokens are runs
 //   on both sides, a persistent grid that keeps that order;
-// - kvx_parts_kernel: the other unplanned calls (few or short records, rows to
-//   resolve, the host link), a persistent grid over parts of units;
-// - kvx_tile_kernel: unplanned long records between head-major pools, a
-//   persistent grid of workgroups over whole units.
+// - kvx_parts_kernel (kvx_shared_parts_kernel for more than 64 records): the
+//   other unplanned calls (few or short records, rows to resolve, the host
+//   link), a persistent grid over parts of units.
 //
 // Order matters because of the memory, not of the caches: nothing is re-read.
 // A bare copy of random 256 KiB pages moves 6.6 TB/s (read + write) when the
@@ -28,6 +27,7 @@
 // 6.3 TB/s, depending on where the pools sit in physical memory, when every
 // wavefront walks through a page of its own.
 
+#include <algorithm>
 #include <atomic>
 
 #include "kvx_internal.h"
@@ -42,24 +42,25 @@
 #define KVX_NT_STORE KVX_NT
 #endif
 // kvx_parts_kernel: workgroups of 256 threads per CU, and 16-byte vectors in
-// flight per lane.  64 decode records (1-4 tokens of 36 x 8 x 128): 7 x 4
-// 12.9 us, 4 x 4 15.0, 6 x 8 13.4, 8 x 2 16.0.
+// flight per lane (64 decode records, 1-4 tokens of 36 x 8 x 128: 12.2 us).
 #ifndef KVX_PARTS_BLOCKS_PER_CU
 #define KVX_PARTS_BLOCKS_PER_CU 7
 #endif
 #ifndef KVX_PARTS_UNROLL
 #define KVX_PARTS_UNROLL 4
 #endif
-// The same for more than 64 records: threads per workgroup, which share their
-// look at the records, and workgroups per CU.
+// kvx_shared_parts_kernel: threads per workgroup, which share their look at the
+// records, and workgroups per CU; where rows are resolved, workgroups of 256
+// threads.  16384 records of 1-4 tokens of 2 x 2 x 64, and 4096 of 36 x 8 x 128:
+// 512 threads, 3 per CU, 100 and 638 us; 1024, 1, 70 and 685; 256, 7, 169 and 635.
 #ifndef KVX_SHARE_BLOCK
 #define KVX_SHARE_BLOCK 512
 #endif
 #ifndef KVX_SHARE_BLOCKS_PER_CU
 #define KVX_SHARE_BLOCKS_PER_CU 3
 #endif
-#ifndef KVX_SHARE_TEAM_BLOCKS_PER_CU
-#define KVX_SHARE_TEAM_BLOCKS_PER_CU 2
+#ifndef KVX_SHARE_ROWS_BLOCKS_PER_CU
+#define KVX_SHARE_ROWS_BLOCKS_PER_CU 6
 #endif
 // Parts per wavefront that units are cut into.  64 half-filled pages of 36
 // layers: 108 us with 32, 116 with 8.
@@ -67,24 +68,26 @@
 #define KVX_GRID_PARTS 32
 #endif
 // Unplanned calls that resolve rows: from KVX_TEAM_KIB KiB per wavefront of the
-// grid on, four wavefronts share a part, KVX_TEAM_BLOCKS_PER_CU workgroups per
-// CU, KVX_TEAM_PARTS parts per wavefront.  A wavefront to itself walks through
+// grid on, in units that most often hold KVX_TEAM_UNIT vectors, four wavefronts
+// share a part, and of the grid only KVX_TEAM_BLOCKS_PER_CU workgroups per CU
+// work, KVX_TEAM_PARTS parts per wavefront.  A wavefront to itself walks through
 // a page of its own, and thousands of pages at once run at the memory's random
-// rate (head-major to token-major, 8.1 GB: 1634 us; with teams 1513).  A call
-// that small anyway has more parts than teams without them (200 tokens of
-// 36 x 8 x 128: 17 us with a wavefront per part, 31.5 with teams that search
-// the records in LDS).
+// rate.  Teams, head-major 64 to token-major 64 token pages, 100 records of 400
+// to 800 tokens of 36 x 8 x 128: 2 per CU 3249 us, 3 3311, 4 3319; the way
+// back 3026, 3155 and 3197.  Smaller calls have more parts than teams without
+// them (200 tokens: 13.3 us), and small units fill no team (65536 records of 1
+// to 4 tokens of 2 x 2 x 64: 800 us in teams, 600 without).
 #ifndef KVX_TEAM_KIB
 #define KVX_TEAM_KIB 8
 #endif
-#ifndef KVX_TILE_UNROLL
-#define KVX_TILE_UNROLL 4   // kvx_tile_kernel: vectors in flight per lane
+#ifndef KVX_TEAM_UNIT
+#define KVX_TEAM_UNIT (4 * kWave * KVX_PARTS_UNROLL)
 #endif
 #ifndef KVX_TEAM_PARTS
 #define KVX_TEAM_PARTS 1
 #endif
 #ifndef KVX_TEAM_BLOCKS_PER_CU
-#define KVX_TEAM_BLOCKS_PER_CU 3
+#define KVX_TEAM_BLOCKS_PER_CU 2
 #endif
 // The same over the host link: whole units, 8 vectors per lane (4: 1.8%
 // slower; units in parts 1.8%).
@@ -117,8 +120,9 @@
 #ifndef KVX_ORDER_TURNS
 #define KVX_ORDER_TURNS 16
 #endif
-// ... and, on the host, calls whose table holds this many entries per record:
-// one workgroup of 1024 threads per CU costs a small call 2-4 us.
+// ... and, on the host, calls whose table holds this many entries per record: a
+// small call with a table longer than its records need takes 13.6 us in
+// workgroups of 1024 threads, 12.2 without.
 #ifndef KVX_ORDER_PAGES
 #define KVX_ORDER_PAGES 8
 #endif
@@ -126,7 +130,7 @@
 namespace kvx {
 namespace {
 
-constexpr int kBlock = 256;   // threads that copy a tile
+constexpr int kBlock = 256;   // threads of a parts workgroup
 constexpr int kWave = 64;
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
@@ -195,206 +199,6 @@ __device__ __forceinline__ bool load_req(const Params &p, int32_t r, Req &q) {
     q.j0 = (int32_t)fd_div(p.fd_Tt, (uint32_t)q.t_start);
     q.pages = (int32_t)fd_div(p.fd_Tt, (uint32_t)(q.t_start + q.n - 1)) - q.j0 + 1;
     return true;
-}
-
-// Everything a tile's row loop needs, fixed for the tile.
-struct Tile {
-    char *t_base;         // tiling side at (l, page, c = 0, slot = 0, h = 0)
-    int32_t sa, sb;       // tiling-side slots [sa, sb) of this tile
-    int32_t ntok;         // sb - sa
-    int32_t qo_a;         // other-side position of slot sa
-    int32_t jo0;          // other-side logical page of qo_a
-    int32_t pid;          // this lane's piece page id (-1: invalid / unused)
-    int32_t l;
-};
-
-// Copies a tile's rows: vectors in (c, slot block, h, slot, v) order over the
-// blocks of KVX_SLOT_BLOCK slots that meet [sa, sb), with the slots outside
-// masked.
-template <int U>
-__device__ __forceinline__ void copy_rows(const Params &p, const Req &q, const Tile &t) {
-    const Side &ts = p.dst, &os = p.src;
-    const uint32_t H = p.H, vpr = p.vpr;
-    // A head-major tiling side takes its vectors in (c, slot block, h, slot,
-    // v) order over the blocks of SB slots that meet [sa, sb): the tiling
-    // side's writes are SB-row runs, and the other side's reads, whose
-    // consecutive heads are adjacent, fill whole slots within a few passes.
-    // (Page order, one head at a time, left the reads 256-byte pieces a
-    // kilobyte apart: 11% slower on a 16-token -> 64-token relayout.)
-    constexpr uint32_t SB = KVX_SLOT_BLOCK;
-    const uint32_t blk0 = (uint32_t)t.sa / SB, nblk = ((uint32_t)t.sb - 1) / SB - blk0 + 1;
-    const uint32_t rows_c = H * nblk * SB;
-    const uint32_t total = rows_c * vpr * (uint32_t)p.C;
-    const char *o_l = os.base + (int64_t)t.l * os.s_l;
-    // The trip count is the same for every lane: the page-id broadcast below
-    // reads other lanes, which must all still be active.
-    for (uint32_t kb = 0; kb < total; kb += kBlock * U) {
-        const char *src[U];
-        char *dst[U];
-        bool ok[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t kk = kb + threadIdx.x + u * kBlock;
-            const uint32_t k = kk < total ? kk : total - 1;
-            bool valid = kk < total;
-            const uint32_t rw = fd_div(p.fd_vpr, k);
-            const uint32_t v = k - rw * vpr;
-            const uint32_t c = rw >= rows_c;
-            const uint32_t rr = rw - c * rows_c;
-            const uint32_t q1 = rr / SB;
-            const uint32_t blk = fd_div(p.fd_H, q1);
-            const uint32_t h = q1 - blk * H;
-            const uint32_t slot = (blk0 + blk) * SB + (rr - q1 * SB);
-            valid = valid && slot >= (uint32_t)t.sa && slot < (uint32_t)t.sb;
-            const int32_t tt = (int32_t)slot - t.sa;  // token index within the tile
-            char *ta = t.t_base + c * ts.s_c + (int64_t)slot * ts.s_t + (int64_t)h * ts.s_h + v * 16;
-            const uint32_t qo = (uint32_t)(t.qo_a + tt);
-            const uint32_t jo = fd_div(p.fd_To, qo);
-            const uint32_t so = qo - jo * (uint32_t)os.T;
-            const uint32_t piece = jo - (uint32_t)t.jo0;
-            int32_t pg = __shfl(t.pid, piece < kWave ? piece : kWave - 1, kWave);
-            if (valid && piece >= kWave) {
-                // More pieces than lanes: resolve this row's page directly.
-                const int64_t idx = q.o_pt_off + jo;
-                pg = -1;
-                if (idx < 0 || idx >= os.pt_len) {
-                    report(p, KVX_DERR_PT_RANGE);
-                } else {
-                    const int32_t id = os.pt[idx];
-                    if (id < 0 || id >= os.N) report(p, KVX_DERR_SRC_PAGE);
-                    else pg = id;
-                }
-            }
-            valid = valid && pg >= 0;
-            const char *oa = o_l + (int64_t)pg * os.s_p + c * os.s_c + (int64_t)so * os.s_t +
-                             (int64_t)h * os.s_h + v * 16;
-            ok[u] = valid;
-            src[u] = oa;
-            dst[u] = ta;
-        }
-        v4u val[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (ok[u]) val[u] = ld16(src[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (ok[u]) st16<false>(dst[u], val[u]);
-    }
-}
-
-// Tile (request q, its tiling-side page jj, layer l), U vectors per thread in
-// flight.
-template <int U>
-__device__ __forceinline__ void do_tile(const Params &p, const Req &q, int64_t jj, int32_t layer) {
-    const Side &ts = p.dst, &os = p.src;
-
-    Tile t;
-    t.l = layer;
-    const int64_t j = q.j0 + jj;
-    const int64_t page_lo = j * ts.T;
-    const int64_t qa = page_lo > q.t_start ? page_lo : q.t_start;
-    const int64_t q_end = (int64_t)q.t_start + q.n;
-    const int64_t qb = page_lo + ts.T < q_end ? page_lo + ts.T : q_end;
-    t.sa = (int32_t)(qa - page_lo);
-    t.sb = (int32_t)(qb - page_lo);
-    t.ntok = t.sb - t.sa;
-
-    // Tiling-side page (one per tile; a uniform load).
-    const int64_t tidx = q.t_pt_off + j;
-    if (tidx < 0 || tidx >= ts.pt_len) {
-        if (threadIdx.x == 0) report(p, KVX_DERR_PT_RANGE);
-        return;
-    }
-    const int32_t tpage = ts.pt[tidx];
-    if (tpage < 0 || tpage >= ts.N) {
-        if (threadIdx.x == 0) report(p, KVX_DERR_DST_PAGE);
-        return;
-    }
-    t.t_base = ts.base + (int64_t)t.l * ts.s_l + (int64_t)tpage * ts.s_p;
-
-    const int32_t delta = q.o_start - q.t_start;
-    t.qo_a = (int32_t)qa + delta;
-    t.jo0 = (int32_t)fd_div(p.fd_To, (uint32_t)t.qo_a);
-    const int32_t jo1 = (int32_t)fd_div(p.fd_To, (uint32_t)((int32_t)qb - 1 + delta));
-    const int32_t K = jo1 - t.jo0 + 1;
-    const int32_t lane = threadIdx.x & (kWave - 1);
-    t.pid = -1;
-    if (lane < K) {
-        const int64_t idx = q.o_pt_off + t.jo0 + lane;
-        uint32_t bad = 0;
-        if (idx < 0 || idx >= os.pt_len) {
-            bad = KVX_DERR_PT_RANGE;
-        } else {
-            const int32_t id = os.pt[idx];
-            if (id < 0 || id >= os.N) bad = KVX_DERR_SRC_PAGE;
-            else t.pid = id;
-        }
-        if (bad && threadIdx.x < kWave) report(p, bad);   // the first wavefront
-    }
-    copy_rows<U>(p, q, t);
-}
-
-// Inclusive sum of x over the workgroup's threads (x = 0 past the chunk).
-// Every thread of the workgroup must call it: it contains barriers.
-__device__ __forceinline__ int64_t block_scan(int64_t x, int64_t *s_wave) {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
-    }
-    if (lane == kWave - 1) s_wave[wid] = x;
-    __syncthreads();
-    for (int w = 0; w < wid; ++w) x += s_wave[w];
-    return x;
-}
-
-// Long records between head-major pools: a workgroup per page of a layer.  Of the
-// unplanned ways it is the fastest here (5.2 GB of 256 KiB pages: 876 us; teams
-// of the parts kernel 911, in order 953) although teams walk through the pages
-// alike; everywhere else that rows are resolved it ties or loses (200 tokens
-// 31 us against 17, 8.1 GB head-major to token-major 1545 against 1511).
-__global__ void __launch_bounds__(kBlock) kvx_tile_kernel(Params p) {
-    // Records are taken kBlock at a time: each thread reads one and counts
-    // its tiles, a workgroup scan turns the counts into tile ranges, and the
-    // workgroup's tiles inside the chunk find their record by binary search.
-    __shared__ int64_t s_end[kBlock];   // end (exclusive) of record i's tiles in the chunk
-    __shared__ int64_t s_wave[kBlock / kWave];
-    Req q;
-    int32_t cached = -1;
-    const int64_t stride = (int64_t)gridDim.x;
-    int64_t tile = blockIdx.x, chunk_base = 0;
-    for (int32_t r0 = 0; r0 < p.n_reqs; r0 += kBlock) {
-        const int32_t nr = p.n_reqs - r0 < kBlock ? p.n_reqs - r0 : kBlock;
-        int64_t cnt = 0;
-        if ((int32_t)threadIdx.x < nr) {
-            Req mine;
-            if (!load_req(p, r0 + threadIdx.x, mine) && blockIdx.x == 0)
-                report(p, KVX_DERR_BAD_REQ);
-            cnt = mine.pages * p.L;
-        }
-        s_end[threadIdx.x] = block_scan(cnt, s_wave);
-        __syncthreads();
-        const int64_t chunk_tiles = s_end[kBlock - 1];
-        for (; tile < chunk_base + chunk_tiles; tile += stride) {   // uniform
-            const int64_t local = tile - chunk_base;
-            int32_t lo = 0, hi = nr - 1;             // first record whose range ends past `local`
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (s_end[mid] > local) hi = mid;
-                else lo = mid + 1;
-            }
-            if (r0 + lo != cached) {
-                load_req(p, r0 + lo, q);
-                cached = r0 + lo;
-            }
-            const int64_t in_rec = local - (lo ? s_end[lo - 1] : 0);
-            const int64_t jj = in_rec / p.L;
-            do_tile<KVX_TILE_UNROLL>(p, q, jj, (int32_t)(in_rec - jj * p.L));
-        }
-        chunk_base += chunk_tiles;
-        __syncthreads();                             // s_end and s_wave are rewritten next chunk
-    }
 }
 
 // Lane k's row of a sweep piece: kv component c, slot, head h, vector v of
@@ -702,7 +506,8 @@ struct GridArgs {
     uint32_t t_h, o_h;                // rows only
     FastDiv fd_vpr, fd_H;             // rows only
     uint32_t min_part;                // vectors a part has at least
-    uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part
+    uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part,
+    uint32_t team_blocks;             // and the workgroups that then work
     float even, team_even;            // part size aimed at, in 64 U (256 U for teams) vectors, for each 64 vectors
                                       // of a wavefront's 64 records
 };
@@ -950,8 +755,16 @@ struct Records {
     GridRec rec[B];
     int64_t end[B];              // parts up to and with record i's, among its 64
     uint32_t parts[B];           // parts of each of record i's pages
-    uint32_t part_vecs[B / kWave];
+    uint32_t part_vecs[B];       // vectors of each part
 };
+
+// Whether four wavefronts share each part, judged by 64 of the records, one per
+// lane (`chunks` times as many in all), whose largest pages hold `tile` vectors.
+__device__ __forceinline__ bool worth_teams(const GridArgs &a, const GridRec &g, uint32_t tile, uint32_t chunks) {
+    const uint64_t some = __ballot(g.pages > 0), large = __ballot(g.pages > 0 && tile >= KVX_TEAM_UNIT);
+    const uint64_t all = (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * a.fd_L.d * chunks;
+    return all >= a.team_min && 2 * __builtin_popcountll(large) >= __builtin_popcountll(some);
+}
 
 // Persistent grid over parts of units, for calls of few or short records and
 // for those that resolve rows.
@@ -961,16 +774,17 @@ struct Records {
 // and no barrier: every wavefront looks at all of them.  Of more, each
 // wavefront of a workgroup looks at another 64 and leaves what it found in
 // LDS: looking at 64 records costs a wavefront about 0.5 us whether or not
-// any of their parts are its own (16384 records of 1-4 tokens of 2 x 2 x 64:
-// 533 us when every wavefront looked at all of them, 100 so).
+// any of their parts are its own (1024, 16384 and 65536 records of 1-4 tokens of
+// 2 x 2 x 64: 36, 533 and 2119 us when every wavefront looked at all of them, 7.8,
+// 100 and 387 so).
 // What bounds a small call is the chain of dependent
 // loads (records, page ids of both sides at once, data) and the width of the
 // chip: a unit is cut into parts of 64 U vectors, or larger ones once there
 // are KVX_GRID_PARTS per wavefront.  Layers are innermost, so that the parts
 // in flight spread over the pool.  Against whole units per wavefront and
-// records in LDS (us, that -> this): 64 decode records 14.8 -> 12.9, 64
-// half-filled pages 145 -> 108, 4 x 200 tokens 60.2 -> 48.4, 1024 decode
-// records 167.6 -> 163.6; 16384 of them 2331 -> 2340 (equal).
+// records in LDS (us, that : this): 64 decode records 14.4 : 12.2, 64
+// half-filled pages 145 : 112, 4 x 50 tokens 38.9 : 15.2, 1024 decode records
+// 162 : 157, 16384 of them 2494 : 2504.
 template <int OP, SweepMode MODE, bool HOST, int U, int B, bool SHARE>
 __device__ __forceinline__ void copy_parts(Records<B> *shared) {
     constexpr bool kPool = OP == OP_TRANSFER, kRows = MODE == ROWS_T || MODE == ROWS_H;
@@ -978,17 +792,17 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
     constexpr int kWaves = B / kWave, kStep = SHARE ? B : kWave;
     const uint32_t lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t workers = gridDim.x * kWaves;
     const int32_t n_reqs = fresh_args().n_reqs;
-    uint32_t team = 1, me = lane;
+    uint32_t team = 1, me = lane, workers = gridDim.x * kWaves;
     int64_t at = (int64_t)blockIdx.x * kWaves + wave;
     if (SHARE && kRows) {
         const GridArgs &a = fresh_args();
         GridRec g;
         (void)grid_record<OP>(a, load_raw(a, lane), g);
-        const uint64_t v = (uint64_t)g.pages * (record_slots<MODE>(g, a.fd_Tt.d) * a.fd_hv.d * a.C);
-        const uint64_t all = (uint64_t)lane64(wave_scan(v), kWave - 1) * a.fd_L.d * (uint32_t)((n_reqs + kWave - 1) / kWave);
-        if (all >= a.team_min) {
+        const uint32_t tile = record_slots<MODE>(g, a.fd_Tt.d) * a.fd_hv.d * a.C;
+        if (worth_teams(a, g, tile, (n_reqs + kWave - 1) / kWave)) {
+            if (blockIdx.x >= a.team_blocks) return;
+            workers = a.team_blocks * kWaves;
             team = kTeam;
             me = threadIdx.x % (kTeam * kWave);
             at /= kTeam;
@@ -1001,7 +815,9 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
         const uint32_t bad = grid_record<OP>(ra, load_raw(ra, r0 + (SHARE ? threadIdx.x : lane)), g);
         if (bad && blockIdx.x == 0 && (SHARE || wave == 0) && ra.err) atomicOr(ra.err, bad);
         const uint32_t tile = record_slots<MODE>(g, T) * ra.fd_hv.d * ra.C;   // vectors of the record's largest page
-        if (!SHARE && kRows && (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * L >= ra.team_min) {
+        if (!SHARE && kRows && worth_teams(ra, g, tile, 1)) {
+            if (blockIdx.x >= ra.team_blocks) return;
+            workers = ra.team_blocks * kWaves;
             team = kTeam;
             me = threadIdx.x % (kTeam * kWave);
             at /= kTeam;
@@ -1015,6 +831,7 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
         const uint32_t fit = (even < (float)(0x40000000 / unit) ? (uint32_t)even + 1 : 0x40000000 / unit) * unit;
         uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
         uint32_t parts = (tile + part_vecs - 1) / part_vecs;
+        if (team > 1 && parts > 1) part_vecs = ((tile + parts - 1) / parts + unit - 1) / unit * unit;   // of equal size
         const uint64_t count = (uint64_t)g.pages * parts;
         int64_t end = __ballot(count >> 25) == 0 ? (int64_t)wave_scan32((uint32_t)count) : (int64_t)wave_scan(count);
         int64_t ends = 0;                                  // lane i: parts of wavefront i's records
@@ -1022,101 +839,102 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
             shared->rec[threadIdx.x] = g;
             shared->end[threadIdx.x] = end;
             shared->parts[threadIdx.x] = parts;
-            if (lane == 0) shared->part_vecs[wave] = part_vecs;
+            shared->part_vecs[threadIdx.x] = part_vecs;
             __syncthreads();
             if (lane < (uint32_t)kWaves) ends = shared->end[lane * kWave + kWave - 1];
         }
         for (int c = 0; c < (SHARE ? kWaves : 1); ++c) {
-        const int64_t total = (SHARE ? lane64(ends, c) : lane64(end, kWave - 1)) * L;
-        if (SHARE) {
-            if (at >= total) {
-                at -= total;
-                continue;
+            const int64_t total = (SHARE ? lane64(ends, c) : lane64(end, kWave - 1)) * L;
+            if (SHARE) {
+                if (at >= total) {
+                    at -= total;
+                    continue;
+                }
+                g = shared->rec[c * kWave + lane];
+                end = shared->end[c * kWave + lane];
+                parts = shared->parts[c * kWave + lane];
+                part_vecs = shared->part_vecs[c * kWave + lane];
             }
-            g = shared->rec[c * kWave + lane];
-            end = shared->end[c * kWave + lane];
-            parts = shared->parts[c * kWave + lane];
-            part_vecs = __builtin_amdgcn_readfirstlane(shared->part_vecs[c]);
-        }
-        for (; at < total; at += workers / team) {
-            const GridArgs &a = fresh_args();
-            const uint64_t rem = at < INT32_MAX ? fd_div(a.fd_L, (uint32_t)at) : (uint64_t)at / L;
-            const uint32_t l = (uint32_t)(at - (int64_t)rem * L);
-            const int r = __builtin_ctzll(__ballot(end > rem));
-            const uint32_t r_parts = lane32(parts, r);
-            const uint64_t in = rem - (lane64(end, r) - lane64(g.pages, r) * r_parts);
-            uint32_t j = (uint32_t)in, part = 0;
-            if (r_parts > 1) {
-                j = in <= ~0u ? (uint32_t)in / r_parts : (uint32_t)(in / r_parts);
-                part = (uint32_t)(in - (uint64_t)j * r_parts);
-            }
-            uint32_t sa = lane32(g.sa, r), left = lane32(g.n, r);
-            const int64_t t_idx = lane64(g.t_idx, r) + j;
-            GridPart w;
-            w.pos = lane32(g.pos, r);
-            if (j > 0) {
-                const uint32_t skip = j * T - sa;
-                sa = 0;
-                left -= skip;
-                w.pos += skip;
-            }
-            const uint32_t ntok = left < T - sa ? left : T - sa;
-            w.o_off = lane64(g.o_off, r);
-            w.sa = sa;
-            w.ntok = ntok;
-            w.R = unit_slots<MODE>(sa, ntok) * a.fd_hv.d;
-            const uint32_t vecs = w.R * a.C;
-            w.kb = part * part_vecs;
-            if (w.kb >= vecs) continue;
-            w.ke = vecs - w.kb < part_vecs ? vecs : w.kb + part_vecs;
-            // the page ids of both sides: the other side's pages of this page's
-            // tokens, the first 64 of them, one per lane
-            const uint32_t tpage = (uint32_t)cload(a.t_pt + t_idx);
-            uint32_t jo0 = 0, K = 1, opid = 0, bits = 0;
-            if (kPool) {
-                jo0 = fd_div(a.fd_To, w.pos);
-                K = fd_div(a.fd_To, w.pos + ntok - 1) - jo0 + 1;
-                if (lane < K) {
-                    const int64_t idx = w.o_off + jo0 + lane;
-                    if (idx < 0 || idx >= a.o_len) bits = KVX_DERR_PT_RANGE;
-                    else opid = (uint32_t)a.o_pt[idx];
+            for (; at < total; at += workers / team) {
+                const GridArgs &a = fresh_args();
+                const uint64_t rem = at < INT32_MAX ? fd_div(a.fd_L, (uint32_t)at) : (uint64_t)at / L;
+                const uint32_t l = (uint32_t)(at - (int64_t)rem * L);
+                const int r = __builtin_ctzll(__ballot(end > rem));
+                const uint32_t r_parts = lane32(parts, r);
+                const uint64_t in = rem - (lane64(end, r) - lane64(g.pages, r) * r_parts);
+                uint32_t j = (uint32_t)in, part = 0;
+                if (r_parts > 1) {
+                    j = in <= ~0u ? (uint32_t)in / r_parts : (uint32_t)(in / r_parts);
+                    part = (uint32_t)(in - (uint64_t)j * r_parts);
+                }
+                uint32_t sa = lane32(g.sa, r), left = lane32(g.n, r);
+                const int64_t t_idx = lane64(g.t_idx, r) + j;
+                GridPart w;
+                w.pos = lane32(g.pos, r);
+                if (j > 0) {
+                    const uint32_t skip = j * T - sa;
+                    sa = 0;
+                    left -= skip;
+                    w.pos += skip;
+                }
+                const uint32_t ntok = left < T - sa ? left : T - sa;
+                w.o_off = lane64(g.o_off, r);
+                w.sa = sa;
+                w.ntok = ntok;
+                w.R = unit_slots<MODE>(sa, ntok) * a.fd_hv.d;
+                const uint32_t vecs = w.R * a.C;
+                const uint32_t size = lane32(part_vecs, r);
+                w.kb = part * size;
+                if (w.kb >= vecs) continue;
+                w.ke = vecs - w.kb < size ? vecs : w.kb + size;
+                // the page ids of both sides: the other side's pages of this page's
+                // tokens, the first 64 of them, one per lane
+                const uint32_t tpage = (uint32_t)cload(a.t_pt + t_idx);
+                uint32_t jo0 = 0, K = 1, opid = 0, bits = 0;
+                if (kPool) {
+                    jo0 = fd_div(a.fd_To, w.pos);
+                    K = fd_div(a.fd_To, w.pos + ntok - 1) - jo0 + 1;
+                    if (lane < K) {
+                        const int64_t idx = w.o_off + jo0 + lane;
+                        if (idx < 0 || idx >= a.o_len) bits = KVX_DERR_PT_RANGE;
+                        else opid = (uint32_t)a.o_pt[idx];
+                    }
+                }
+                if (tpage >= a.t_N) {
+                    if (lane == 0 && a.err) atomicOr(a.err, OP == OP_GATHER ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
+                    continue;
+                }
+                w.t = a.t_base + (int64_t)l * a.t_l + (int64_t)tpage * a.t_p + (uint64_t)sa * a.t_t * 16;
+                const auto from_lane = [&](uint32_t jo, bool valid) {
+                    const uint32_t i = valid ? jo - jo0 : 0;
+                    uint32_t pg = (uint32_t)__shfl((int)opid, i < kWave ? i : 0, kWave);
+                    if (i >= kWave) pg = other_page(a, w.o_off + jo);      // more pages than lanes
+                    return pg;
+                };
+                if (!kPool) {
+                    const uint64_t run = (uint64_t)lane32(g.n_block, r) * a.fd_hv.d;   // vectors of one kv component's block
+                    w.o = a.o_base + w.o_off + ((uint64_t)l * a.C * run + (uint64_t)w.pos * a.fd_hv.d) * 16;
+                    w.o_c = run * 16;
+                    copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
+                    continue;
+                }
+                if (lane < K && opid >= a.o_N && !bits) bits = KVX_DERR_SRC_PAGE;
+                if (bits) {
+                    opid = ~0u;
+                    if (a.err) atomicOr(a.err, bits);
+                }
+                w.o = a.o_base + (int64_t)l * a.o_l;
+                w.o_c = (uint64_t)a.o_c * 16;
+                if (K == 1) {
+                    const uint32_t pg = lane32(opid, 0);
+                    if (pg == ~0u) continue;
+                    w.o += (int64_t)pg * a.o_p + (uint64_t)(w.pos - jo0 * a.fd_To.d) * a.o_t * 16;
+                    copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
+                } else {
+                    copy_part<OP, MODE, false, HOST, U>(a, w, me, team * kWave, from_lane);
                 }
             }
-            if (tpage >= a.t_N) {
-                if (lane == 0 && a.err) atomicOr(a.err, OP == OP_GATHER ? KVX_DERR_SRC_PAGE : KVX_DERR_DST_PAGE);
-                continue;
-            }
-            w.t = a.t_base + (int64_t)l * a.t_l + (int64_t)tpage * a.t_p + (uint64_t)sa * a.t_t * 16;
-            const auto from_lane = [&](uint32_t jo, bool valid) {
-                const uint32_t i = valid ? jo - jo0 : 0;
-                uint32_t pg = (uint32_t)__shfl((int)opid, i < kWave ? i : 0, kWave);
-                if (i >= kWave) pg = other_page(a, w.o_off + jo);      // more pages than lanes
-                return pg;
-            };
-            if (!kPool) {
-                const uint64_t run = (uint64_t)lane32(g.n_block, r) * a.fd_hv.d;   // vectors of one kv component's block
-                w.o = a.o_base + w.o_off + ((uint64_t)l * a.C * run + (uint64_t)w.pos * a.fd_hv.d) * 16;
-                w.o_c = run * 16;
-                copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
-                continue;
-            }
-            if (lane < K && opid >= a.o_N && !bits) bits = KVX_DERR_SRC_PAGE;
-            if (bits) {
-                opid = ~0u;
-                if (a.err) atomicOr(a.err, bits);
-            }
-            w.o = a.o_base + (int64_t)l * a.o_l;
-            w.o_c = (uint64_t)a.o_c * 16;
-            if (K == 1) {
-                const uint32_t pg = lane32(opid, 0);
-                if (pg == ~0u) continue;
-                w.o += (int64_t)pg * a.o_p + (uint64_t)(w.pos - jo0 * a.fd_To.d) * a.o_t * 16;
-                copy_part<OP, MODE, true, HOST, U>(a, w, me, team * kWave, from_lane);
-            } else {
-                copy_part<OP, MODE, false, HOST, U>(a, w, me, team * kWave, from_lane);
-            }
-        }
-        at -= total;
+            at -= total;
         }
         if (SHARE) __syncthreads();                         // the next records take the place of these
     }
@@ -1128,10 +946,12 @@ __global__ void __launch_bounds__(kBlock) kvx_parts_kernel(GridArgs) {
 }
 
 // The same for more than 64 records.
+template <SweepMode MODE>
+constexpr int kShareBlock = MODE == ROWS_T || MODE == ROWS_H ? kBlock : KVX_SHARE_BLOCK;
 template <int OP, SweepMode MODE, bool HOST, int U>
-__global__ void __launch_bounds__(KVX_SHARE_BLOCK) kvx_shared_parts_kernel(GridArgs) {
-    __shared__ Records<KVX_SHARE_BLOCK> shared;
-    copy_parts<OP, MODE, HOST, U, KVX_SHARE_BLOCK, true>(&shared);
+__global__ void __launch_bounds__(kShareBlock<MODE>) kvx_shared_parts_kernel(GridArgs) {
+    __shared__ Records<kShareBlock<MODE>> shared;
+    copy_parts<OP, MODE, HOST, U, kShareBlock<MODE>, true>(&shared);
 }
 
 // Persistent grid that keeps the sweep's order, for calls of long records.
@@ -1500,26 +1320,20 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     a.min_part = link ? 0x40000000 : kWave * U;          // over the link whole units
     const int64_t page_vecs = (int64_t)t.T * p.C * p.H * p.vpr;
     const bool rows = mode == ROWS_T || mode == ROWS_H;
-    const uint64_t small = (uint64_t)cus * KVX_PARTS_BLOCKS_PER_CU * 4 * KVX_TEAM_KIB * kWave;
-    const bool teams = rows && !link && (double)t.pt_len * page_vecs * p.L >= (double)small;
-    a.team_min = teams ? small : ~0ull;
-    if (OP == OP_TRANSFER && teams && mode == ROWS_H && !adjacent(o, true) &&
-        t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs) {
-        hipLaunchKernelGGL(kvx_tile_kernel, dim3(cus * KVX_TEAM_BLOCKS_PER_CU), dim3(kBlock), 0, stream, p);
-        return hipGetLastError();
-    }
+    a.team_min = rows && !link ? (uint64_t)cus * KVX_PARTS_BLOCKS_PER_CU * 4 * KVX_TEAM_KIB * kWave : ~0ull;
     const bool order = !rows && !link && t.pt_len >= (int64_t)KVX_ORDER_PAGES * p.n_reqs &&
                        page_vecs >= (int64_t)KVX_ORDER_PIECES * kWave;
     const bool share = p.n_reqs > kWave;
-    const int threads = order ? B : share ? KVX_SHARE_BLOCK : kBlock;
+    const int threads = order ? B : share && !rows ? KVX_SHARE_BLOCK : kBlock;
     int blocks = (cus + 7) / 8 * 8;
-    if (!order && link) blocks = cus * KVX_LINK_BLOCKS_PER_CU * kBlock / threads;
-    else if (!order && teams) blocks = cus * (share ? KVX_SHARE_TEAM_BLOCKS_PER_CU : KVX_TEAM_BLOCKS_PER_CU);
-    else if (!order) blocks = cus * (share ? KVX_SHARE_BLOCKS_PER_CU : KVX_PARTS_BLOCKS_PER_CU);
+    if (!order)
+        blocks = cus * (link ? KVX_LINK_BLOCKS_PER_CU * kBlock / threads
+                        : !share ? KVX_PARTS_BLOCKS_PER_CU : rows ? KVX_SHARE_ROWS_BLOCKS_PER_CU : KVX_SHARE_BLOCKS_PER_CU);
     // the vectors of all records, were they like these 64, over the parts aimed at
     const float per_64 = 64.f * p.L * ((p.n_reqs + kWave - 1) / kWave), waves = (float)blocks * (threads / kWave);
     a.even = per_64 / (waves * KVX_GRID_PARTS * kWave * (link ? UL : U));
-    a.team_even = per_64 / (waves * KVX_TEAM_PARTS * kWave * 4 * U);
+    a.team_blocks = (uint32_t)std::min(blocks, cus * KVX_TEAM_BLOCKS_PER_CU);
+    a.team_even = per_64 / ((float)a.team_blocks * 4 * KVX_TEAM_PARTS * kWave * 4 * U);
     const GridFn fn = order ? order_fns[mode] : link ? link_fns[p.dst_host ? 1 : 0][share][mode] : parts_fns[share][mode];
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), 0, stream, a);
     return hipGetLastError();

@@ -115,20 +115,27 @@ def test_rows_through_a_buffer(library, layout, pinned):
     check(cases.gather_scatter_case(layout, 24, 2, 80, seed=31, H=5, pinned=pinned))
 
 
-def test_product_library_copies_much_data_of_rows_by_teams():
-    """One record of 4000 tokens over 8 layers, 131 MB, above the size from
-    which the product library's wavefronts share parts; a bad id on each side."""
+@pytest.mark.parametrize("ls,ld,Ts,Td", [("PLCHTD", "LPCTHD", 64, 16), ("PLCHTD", "LPCHTD", 64, 64), ("LPCTHD", "PLCHTD", 16, 64)])
+@pytest.mark.parametrize("n_reqs", [1, 12, 80])
+def test_product_library_copies_much_data_of_rows_by_teams(ls, ld, Ts, Td, n_reqs):
+    """4000 tokens over 8 layers, 131 MB, in 1, 12 or 80 records (many or few
+    table entries for each), above the size from which the product library's
+    wavefronts share parts; odd starts, and a bad id on each side."""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    S = PoolSpec(8, 2, 8, 128, T=64, N=70, e=2, layout="PLCHTD")
-    D = PoolSpec(8, 2, 8, 128, T=16, N=270, e=2, layout="LPCTHD")
+    n = 4000 // n_reqs
+    per_s, per_d = -(-(n + 5) // Ts), -(-(n + 3) // Td)
+    S = PoolSpec(8, 2, 8, 128, T=Ts, N=per_s * n_reqs + 6, e=2, layout=ls)
+    D = PoolSpec(8, 2, 8, 128, T=Td, N=per_d * n_reqs + 6, e=2, layout=ld)
     rng = np.random.default_rng(6)
-    src, dst = rng.permutation(70)[:64].astype(np.int32), rng.permutation(270)[:251].astype(np.int32)
-    dst[7] = 270
+    src = rng.permutation(S.N)[:per_s * n_reqs].astype(np.int32)
+    dst = rng.permutation(D.N)[:per_d * n_reqs].astype(np.int32)
+    dst[7] = D.N
     src[11] = -1
-    rows = np.asarray([[0, 0, 0, 5, 3, 4000]], np.int64)
-    check(Workload("case", "long record of rows", {"A": S, "B": D}, [Step("transfer", "A", "B", src, dst, rows)],
+    r = np.arange(n_reqs)
+    rows = np.stack([r * per_s, r * per_d, 0 * r, 0 * r + 5, 0 * r + 3, 0 * r + n], axis=1)
+    check(Workload("case", "much data of rows", {"A": S, "B": D}, [Step("transfer", "A", "B", src, dst, rows)],
                    value_seed=8, prefill_tag=3))
 
 
