@@ -89,10 +89,16 @@
 #ifndef KVX_TEAM_BLOCKS_PER_CU
 #define KVX_TEAM_BLOCKS_PER_CU 2
 #endif
-// The same over the host link: whole units, 8 vectors per lane (4: 1.8%
-// slower; units in parts 1.8%).
+// The same over the host link: 8 vectors per lane (4: 1.8% slower), and units
+// cut into as many parts as make KVX_LINK_PARTS of the call: fewer do not fill
+// the link, and many units in parts are slower.  Out and back, 1 page of 2
+// layers: 27 us, 242 in whole units; 2 x 8 layers 163 (80 parts 165, 320 168,
+// 640 183, whole units 333); 8 x 36 layers 2688 (2684, 2701, 2726, 2692).
 #ifndef KVX_LINK_BLOCKS_PER_CU
 #define KVX_LINK_BLOCKS_PER_CU 5
+#endif
+#ifndef KVX_LINK_PARTS
+#define KVX_LINK_PARTS 160
 #endif
 #ifndef KVX_LINK_UNROLL
 #define KVX_LINK_UNROLL 8
@@ -505,7 +511,6 @@ struct GridArgs {
     FastDiv fd_Tt, fd_To, fd_hv, fd_L;
     uint32_t t_h, o_h;                // rows only
     FastDiv fd_vpr, fd_H;             // rows only
-    uint32_t min_part;                // vectors a part has at least
     uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part,
     uint32_t team_blocks;             // and the workgroups that then work
     float even, team_even;            // part size aimed at, in 64 U (256 U for teams) vectors, for each 64 vectors
@@ -828,8 +833,7 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
         // a part: 64 U vectors, or more when there are many
         const uint32_t unit = kUnit * team;
         const float even = (float)all * (team == 1 ? ra.even : ra.team_even);
-        const uint32_t fit = (even < (float)(0x40000000 / unit) ? (uint32_t)even + 1 : 0x40000000 / unit) * unit;
-        uint32_t part_vecs = fit < ra.min_part ? ra.min_part : fit;
+        uint32_t part_vecs = (even < (float)(0x40000000 / unit) ? (uint32_t)even + 1 : 0x40000000 / unit) * unit;
         uint32_t parts = (tile + part_vecs - 1) / part_vecs;
         if (team > 1 && parts > 1) part_vecs = ((tile + parts - 1) / parts + unit - 1) / unit * unit;   // of equal size
         const uint64_t count = (uint64_t)g.pages * parts;
@@ -1317,7 +1321,6 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
     a.fd_L = make_fastdiv((uint32_t)p.L);
     const bool link = p.src_host || p.dst_host;
-    a.min_part = link ? 0x40000000 : kWave * U;          // over the link whole units
     const int64_t page_vecs = (int64_t)t.T * p.C * p.H * p.vpr;
     const bool rows = mode == ROWS_T || mode == ROWS_H;
     a.team_min = rows && !link ? (uint64_t)cus * KVX_PARTS_BLOCKS_PER_CU * 4 * KVX_TEAM_KIB * kWave : ~0ull;
@@ -1331,7 +1334,7 @@ static int launch_grid(const Params &p, hipStream_t stream) {
                         : !share ? KVX_PARTS_BLOCKS_PER_CU : rows ? KVX_SHARE_ROWS_BLOCKS_PER_CU : KVX_SHARE_BLOCKS_PER_CU);
     // the vectors of all records, were they like these 64, over the parts aimed at
     const float per_64 = 64.f * p.L * ((p.n_reqs + kWave - 1) / kWave), waves = (float)blocks * (threads / kWave);
-    a.even = per_64 / (waves * KVX_GRID_PARTS * kWave * (link ? UL : U));
+    a.even = link ? per_64 / (float)(KVX_LINK_PARTS * kWave * UL) : per_64 / (waves * KVX_GRID_PARTS * kWave * U);
     a.team_blocks = (uint32_t)std::min(blocks, cus * KVX_TEAM_BLOCKS_PER_CU);
     a.team_even = per_64 / ((float)a.team_blocks * 4 * KVX_TEAM_PARTS * kWave * 4 * U);
     const GridFn fn = order ? order_fns[mode] : link ? link_fns[p.dst_host ? 1 : 0][share][mode] : parts_fns[share][mode];

@@ -86,3 +86,22 @@ def test_many_short_records(kvx):
     many = np.stack([r // 32, r // 32, 0 * r, r % 32 * 2, r % 32 * 2, 0 * r + 2], axis=1)
     many, few = least(p.transfer(many), few)
     check(many / few, 14, "16384 short records")
+
+
+@pytest.mark.parametrize("layout", [TOKEN, HEAD])
+def test_few_pages_over_the_link(kvx, layout):
+    """One page of 2 layers out to host memory and back, against 18 times the
+    data (at fault 0.5; 0.08)."""
+    def trip(L):
+        S = PoolSpec(L, 2, 8, 128, T=64, N=8, e=2, layout=layout)
+        B = BufSpec(L, 2, 8, 128, 2, cap=L * 2 * 64 * 8 * 128)
+        p = Pools(kvx, S, S, 1, 1)
+        buf = W.alloc_side(B, "cuda", pinned=True)
+        reqs, pt = kvx.device_reqs(p.rows(64), "cuda"), kvx.device_table(p.tables[0], "cuda")
+
+        def call():
+            kvx.kvx_gather(p.mem[0], S, buf, B, pt, reqs)
+            kvx.kvx_scatter(buf, B, p.mem[1], S, pt, reqs)
+        return call
+    few, many = least(trip(2), trip(36))
+    check(few / many, 0.25, f"{layout}, one page of 2 layers")
