@@ -111,14 +111,18 @@
 #define KVX_ORDER_BLOCK 1024
 #endif
 // Which calls keep the order, judged on the device by the first 64 records:
-// full pages of at least KVX_ORDER_PIECES KiB, three quarters filled, and
-// KVX_ORDER_TURNS KiB to copy per wavefront.  Below them there is no order to
-// keep: 1-4 tokens of 64 records 18.3 us in order, 12.9 in parts; half-filled
-// pages 126 us in order, 108 in parts.  From 64 KiB pages up order wins
-// (64 KiB 1753 against 1925 us, 72 KiB 4751 against 4941, 256 KiB 7146
-// against 8591; on pools that happen to suit the grid 72 KiB pages lose 2%).
+// full pages of at least KVX_ORDER_PIECES KiB, three quarters filled,
+// KVX_ORDER_TURNS KiB to copy per wavefront, and pages of the other side that
+// begin between pieces.  Below them there is no order to keep: 1-4 tokens of 64
+// records 18.3 us in order, 12.2 in parts; half-filled pages 126 us in order, 112
+// in parts.  Order against parts, 32 long prompts and 8 of them (us): 40 KiB
+// pages 4410 : 4347, 217 : 211; 48 KiB 4355 : 4384, 214 : 211; 52 KiB 4366 : 4413,
+// 316 : 326; 56 KiB 4256 : 4404, 315 : 332; 64 KiB 3712 : 4378, 177 : 201; 256 KiB
+// 7245 : 8690.  Where a page of the other side begins inside a piece that piece
+// resolves its rows, and at the barrier all wait for it: MLA's 72 KiB pages from
+// a shifted start 6308 : 4183, 96 KiB of 3 x 80 from one 2208 : 1824.
 #ifndef KVX_ORDER_PIECES
-#define KVX_ORDER_PIECES 40
+#define KVX_ORDER_PIECES 52
 #endif
 #ifndef KVX_ORDER_QUARTERS
 #define KVX_ORDER_QUARTERS 3
@@ -509,6 +513,7 @@ struct GridArgs {
     uint32_t C, elem_shift;
     uint32_t t_c, t_t, o_c, o_t;
     FastDiv fd_Tt, fd_To, fd_hv, fd_L;
+    uint32_t granule;                 // tokens after which a whole number of 64 vectors ends
     uint32_t t_h, o_h;                // rows only
     FastDiv fd_vpr, fd_H;             // rows only
     uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part,
@@ -995,7 +1000,11 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
         const GridArgs &a = fresh_args();
         GridRec g;
         (void)grid_record<OP>(a, load_raw(a, lane), g);
-        const uint32_t T = a.fd_Tt.d, n = g.pages ? (uint32_t)g.n : 0;
+        const uint32_t T = a.fd_Tt.d, To = a.fd_To.d, m = a.granule;
+        // whether the other side's pages begin between pieces
+        const bool between = !kPool || (((uint32_t)(g.pos - g.sa) | T | To) & (m - 1)) == 0;
+        const bool same = kPool && T == To && (uint32_t)g.pos - fd_div(a.fd_To, (uint32_t)g.pos) * To == (uint32_t)g.sa;
+        const uint32_t n = g.pages && (between || same) ? (uint32_t)g.n : 0;
         const uint64_t tokens = (uint64_t)lane64(wave_scan(n), kWave - 1);
         const uint64_t pages = (uint64_t)lane64(wave_scan((uint64_t)g.pages), kWave - 1);
         const uint32_t token_vecs = a.fd_hv.d * a.C;
@@ -1320,6 +1329,8 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     a.fd_To = p.fd_To;
     a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
     a.fd_L = make_fastdiv((uint32_t)p.L);
+    a.granule = kWave;
+    while (a.granule > 1 && a.granule / 2 * (a.fd_hv.d % kWave) % kWave == 0) a.granule /= 2;
     const bool link = p.src_host || p.dst_host;
     const int64_t page_vecs = (int64_t)t.T * p.C * p.H * p.vpr;
     const bool rows = mode == ROWS_T || mode == ROWS_H;

@@ -105,3 +105,15 @@ def test_few_pages_over_the_link(kvx, layout):
         return call
     few, many = least(trip(2), trip(36))
     check(few / many, 0.25, f"{layout}, one page of 2 layers")
+
+
+@pytest.mark.parametrize("H,D,T", [(1, 576, 64), (5, 80, 48)])
+def test_source_pages_that_begin_inside_pieces(kvx, H, D, T):
+    """Long records from and to the middle of pages, whose source pages begin
+    inside the destination's kilobytes, against the same between starts of
+    pages (at fault 1.35 to 1.45; 1.0 to 1.1)."""
+    S = PoolSpec(36, 2, H, D, T=T, N=512, e=2, layout=TOKEN)
+    p = Pools(kvx, S, S, 8, 32)
+    s, d = np.random.default_rng(4).integers(0, T, size=(2, 8))
+    shift, zero = least(p.transfer(p.rows(31 * T, s, d)), p.transfer(p.rows(31 * T)))
+    check(shift / zero, 1.25, f"{H} x {D}, shifted")

@@ -59,6 +59,19 @@ def test_large_pages(library, T, H, D, L, n, shift):
     check(cases.transfer_case("LPCTHD", "PLCTHD", T, T, seed=T + shift, D=D, L=L, C=C, H=H, spec=spec))
 
 
+@pytest.mark.parametrize("Ts,Td", [(48, 48), (64, 64), (32, 64)])
+@pytest.mark.parametrize("H,D", [(5, 80), (8, 128), (3, 56)])
+def test_source_pages_that_begin_inside_pieces(library, Ts, Td, H, D):
+    """1 KiB pieces hold 1.28 tokens, a quarter or 3.05 of them: long records whose
+    source pages begin between and inside pieces (the product library's judge
+    tells them apart), and a page id that is bad."""
+    spec = [(0, 0, 700, None), (37, 5, 500, None), (8, 24, 611, None), (Ts - 1, Td - 1, 300, None)]
+    wl = cases.transfer_case("LPCTHD", "LPCTHD", Ts, Td, seed=Ts + H, D=D, L=16, H=H, spec=spec)
+    check(wl)
+    wl.steps[0].src_pt[9] = -1
+    check(wl)
+
+
 @pytest.mark.parametrize("n_reqs", [63, 64, 65, 1023, 1024, 1025, 2100])
 def test_many_records(library, n_reqs):
     """Around the 64 records of a wavefront and the 1024 of a workgroup, every
