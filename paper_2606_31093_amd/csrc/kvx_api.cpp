@@ -393,6 +393,9 @@ void plan_sweep(kvx::Params &P, const void *plan, int64_t plan_pages, int64_t pl
     P.prefix = static_cast<const int64_t *>(plan);
     P.slots = reinterpret_cast<const kvx_plan_slot *>(P.prefix + P.n_reqs + 1);
     P.plan_pages = plan_pages;
+    // a workgroup per piece of a page, of its average part when pages are sparse
+    // (whatever plan_tokens says, at least one slot's)
+    P.plan_slots = 3 * avg < 2 * full ? (int32_t)std::max<int64_t>(1, (avg + token_bytes - 1) / token_bytes) : P.dst.T;
 }
 
 #ifndef KVX_LAUNCH_CHOICE_DEFAULT

@@ -109,6 +109,7 @@ struct Params {
     // sweep == 0: persistent grid.
     int32_t sweep;
     int64_t plan_pages;
+    int32_t plan_slots;  // slots copied per destination page: all, or their average when pages are sparse
     const int64_t *prefix;
     const kvx_plan_slot *slots;
 };

@@ -446,7 +446,12 @@ __device__ __forceinline__ void sweep_check(const Params &p, uint32_t b, uint32_
 // 7129 us with the checks and the rare paths inline, three passes over the
 // pages; 6613 us so.  72 KiB pages (61 x 576): 4371 to 4238 us; head ranges in
 // 4-layer launches of 300 MB: 499 to 460 us.
-template <SweepMode MODE, bool HOST>
+// SPARSE: a page has a workgroup per piece of its average part (a.ppt), and
+// pages that hold more are copied in turns.  Empty pieces would cost a third to
+// two thirds of copied ones: 256 pages of 256 KiB, 16 of 64 tokens each, in
+// 4-layer launches, 542 us with a workgroup per piece of the whole page, 271 so.
+// Full pages lose 1.2% by the loop, so they have no use for it.
+template <SweepMode MODE, bool HOST, bool SPARSE>
 __global__ void __launch_bounds__(kWave) kvx_sweep_kernel(SweepArgs a, Params) {
     // The second argument is read where it is needed: a piece on the common
     // path needs nothing of it, and its fields would crowd the scalar
@@ -491,9 +496,13 @@ __global__ void __launch_bounds__(kWave) kvx_sweep_kernel(SweepArgs a, Params) {
     d.src_slot = (int32_t)so_a;
     constexpr uint32_t SB = KVX_SWEEP_SLOT_BLOCK;
     const uint32_t slots = MODE == ROWS_H && ntok ? ((sa + ntok - 1) / SB - sa / SB + 1) * SB : ntok;
-    const uint32_t kb = part * kWave;
-    if (kb >= slots * a.fd_hv.d * a.C) return;
-    if (!sweep_piece<MODE, HOST>(a, d, l, kb)) sweep_piece_general<MODE != ROWS_H, HOST>(p, d, l, kb);
+    const uint32_t vecs = slots * a.fd_hv.d * a.C;
+    uint32_t kb = part * kWave;
+    if (kb >= vecs) return;
+    do {
+        if (!sweep_piece<MODE, HOST>(a, d, l, kb)) sweep_piece_general<MODE != ROWS_H, HOST>(p, d, l, kb);
+        kb += a.ppt.d * kWave;
+    } while (SPARSE && kb < vecs);
 }
 
 // What the persistent grid reads of its arguments.  `t` is the tiling side,
@@ -1193,12 +1202,13 @@ static int launch_sweep(const Params &p, hipStream_t stream) {
                           d.s_t >= (int64_t)p.H * p.row_bytes && s.s_t >= (int64_t)p.H * p.row_bytes;
     const SweepMode mode = p.flat ? RUNS : adjacent ? TOKENS : d.tok_contig ? ROWS_T : ROWS_H;
     typedef void (*SweepFn)(SweepArgs, Params);
-    static const SweepFn fns[4][2] = {
-        {kvx_sweep_kernel<RUNS, false>, kvx_sweep_kernel<RUNS, true>},
-        {kvx_sweep_kernel<TOKENS, false>, kvx_sweep_kernel<TOKENS, true>},
-        {kvx_sweep_kernel<ROWS_T, false>, kvx_sweep_kernel<ROWS_T, true>},
-        {kvx_sweep_kernel<ROWS_H, false>, kvx_sweep_kernel<ROWS_H, true>}};
-    const SweepFn fn = fns[mode][p.dst_host ? 1 : 0];
+#define KVX_SWEEPS(mode)                                                                  \
+    {{kvx_sweep_kernel<mode, false, false>, kvx_sweep_kernel<mode, false, true>},          \
+     {kvx_sweep_kernel<mode, true, false>, kvx_sweep_kernel<mode, true, true>}}
+    static const SweepFn fns[4][2][2] = {KVX_SWEEPS(RUNS), KVX_SWEEPS(TOKENS), KVX_SWEEPS(ROWS_T), KVX_SWEEPS(ROWS_H)};
+#undef KVX_SWEEPS
+    const bool sparse = p.plan_slots < d.T;
+    const SweepFn fn = fns[mode][p.dst_host ? 1 : 0][sparse];
     constexpr int64_t SB = KVX_SWEEP_SLOT_BLOCK;
     const int64_t page_slots = mode == ROWS_H ? ((int64_t)d.T + SB - 1) / SB * SB : d.T;
     // bytes from a page's first copied row to the end of its last one
@@ -1207,7 +1217,10 @@ static int launch_sweep(const Params &p, hipStream_t stream) {
     };
     SweepArgs a{};
     a.slots = p.slots;
-    a.ppt = make_fastdiv(sweep_pieces(p, page_slots));
+    // the workgroups of a page: one per piece of as many slots as a page copies
+    const int64_t used = !sparse ? page_slots
+                         : mode == ROWS_H ? ((int64_t)p.plan_slots + SB - 1) / SB * SB : p.plan_slots;
+    a.ppt = make_fastdiv(sweep_pieces(p, used));
     a.pages = make_fastdiv((uint32_t)p.plan_pages);
     const auto fits = [&](const Side &x) {
         return extent(x) <= INT32_MAX && x.s_l / 16 <= UINT32_MAX && x.s_p / 16 <= UINT32_MAX;

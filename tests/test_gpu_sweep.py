@@ -25,7 +25,7 @@ from runner import assert_same, initial_bytes, run_gpu, run_oracle
 pytestmark = pytest.mark.gpu
 
 # the token total passed with a correct plan: only the choice of launch changes
-TOKENS = {"true": lambda t: t, "zero": lambda t: 0, "double": lambda t: 2 * t + 3}
+TOKENS = {"true": lambda t: t, "zero": lambda t: 0, "one": lambda t: 1, "double": lambda t: 2 * t + 3}
 
 
 def planned(tokens="true"):
@@ -340,3 +340,21 @@ def test_product_library_sweeps_dense_small_pages(D, launch):
     wl = cases.transfer_case("LPCTHD", "LPCTHD", 16, 16, seed=D, e=2, D=D, L=3, C=2, H=4, spec=spec)
     check(wl, None)
     assert kvx.kvx_last_launch() == launch
+
+
+@pytest.mark.parametrize("tokens", ["true", "one", "double"])
+@pytest.mark.parametrize("ls,ld,Ts,sl", [("LPCTHD", "LPCTHD", 64, None), ("LPCTHD", "LPCTHD", 16, None),
+                                         ("LPCTHD", "LPCTHD", 64, 7), ("PLCHTD", "LPCTHD", 64, None),
+                                         ("LPCTHD", "PLCHTD", 64, None), ("LPCHTD", "PLCHTD", 16, None)])
+def test_sparse_pages(test_lib, ls, ld, Ts, sl, tokens):
+    """256 KiB pages (7 of 8 heads: 224) that hold a third of their tokens on
+    average: a page has workgroups for that third, and pages that hold more, up
+    to all of it, are copied in turns.  A total of one token leaves the test
+    build one slot's workgroups per page."""
+    n = [1, 64, 16, 17, 20, 40, 3, 15, 31, 12, 8, 9]
+    spec = [(i % 5, (i * 11) % (65 - k), k, None) for i, k in enumerate(n)]
+    wl = cases.transfer_case(ls, ld, Ts, 64, seed=Ts, e=2, D=128, L=3, C=2, H=8, spec=spec)
+    if sl:
+        wl.steps[0].slice = (0, 0, 3, 0, 0, 2, 1, 1, sl)
+    check(wl, test_lib, tokens)
+    check(wl, None, tokens)
