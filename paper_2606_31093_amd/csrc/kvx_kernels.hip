@@ -120,7 +120,9 @@
 // 316 : 326; 56 KiB 4256 : 4404, 315 : 332; 64 KiB 3712 : 4378, 177 : 201; 256 KiB
 // 7245 : 8690.  Where a page of the other side begins inside a piece that piece
 // resolves its rows, and at the barrier all wait for it: MLA's 72 KiB pages from
-// a shifted start 6308 : 4183, 96 KiB of 3 x 80 from one 2208 : 1824.
+// a shifted start 6308 : 4183, 96 KiB of 3 x 80 from one 2208 : 1824.  Where units
+// are taken in turns, all pieces of a unit in several such pages do (64 to 128
+// token pages of 1 x 576, 7.4 GB: 1892 : 1519).
 #ifndef KVX_ORDER_PIECES
 #define KVX_ORDER_PIECES 52
 #endif
@@ -522,7 +524,7 @@ struct GridArgs {
     uint32_t C, elem_shift;
     uint32_t t_c, t_t, o_c, o_t;
     FastDiv fd_Tt, fd_To, fd_hv, fd_L;
-    uint32_t granule;                 // tokens after which a whole number of 64 vectors ends
+    uint32_t granule;                 // tokens after which a whole number of 64 vectors ends; 0: full units in turns
     uint32_t t_h, o_h;                // rows only
     FastDiv fd_vpr, fd_H;             // rows only
     uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part,
@@ -972,6 +974,20 @@ __global__ void __launch_bounds__(kShareBlock<MODE>) kvx_shared_parts_kernel(Gri
     copy_parts<OP, MODE, HOST, U, kShareBlock<MODE>, true>(&shared);
 }
 
+// Wavefronts, of an XCD's W, that take a unit of so many pieces together: as many
+// as it has pieces, or fewer in turns where that leaves fewer of the W idle.
+__host__ __device__ inline uint32_t team_size(uint32_t pieces, uint32_t W) {
+    if (pieces <= W / 8) return pieces;
+    uint32_t size = W, used = 0;
+    for (uint32_t s = 1; s <= 8; ++s) {
+        const uint32_t z = (pieces + s - 1) / s;
+        if (z > W) continue;
+        const uint32_t u = W / z * z;
+        if (u > used + W / 16) used = u, size = z;
+    }
+    return size;
+}
+
 // Persistent grid that keeps the sweep's order, for calls of long records.
 // XCD x copies the units x, x + 8, ...; a team of its wavefronts takes a unit
 // together, 64 vectors (1 KiB) each, and goes on to the unit `teams` further,
@@ -1009,11 +1025,13 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
         const GridArgs &a = fresh_args();
         GridRec g;
         (void)grid_record<OP>(a, load_raw(a, lane), g);
-        const uint32_t T = a.fd_Tt.d, To = a.fd_To.d, m = a.granule;
-        // whether the other side's pages begin between pieces
-        const bool between = !kPool || (((uint32_t)(g.pos - g.sa) | T | To) & (m - 1)) == 0;
-        const bool same = kPool && T == To && (uint32_t)g.pos - fd_div(a.fd_To, (uint32_t)g.pos) * To == (uint32_t)g.sa;
-        const uint32_t n = g.pages && (between || same) ? (uint32_t)g.n : 0;
+        const uint32_t T = a.fd_Tt.d, To = a.fd_To.d;
+        // Whether the other side's pages begin between units, or between pieces
+        // (of units that are not taken in turns).
+        const uint32_t ahead = (uint32_t)g.pos + T - (uint32_t)g.sa;
+        const bool units = ahead == fd_div(a.fd_Tt, ahead) * T && To % T == 0;
+        const bool between = a.granule > 0 && ((ahead | T | To) & (a.granule - 1)) == 0;
+        const uint32_t n = g.pages && (!kPool || units || between) ? (uint32_t)g.n : 0;
         const uint64_t tokens = (uint64_t)lane64(wave_scan(n), kWave - 1);
         const uint64_t pages = (uint64_t)lane64(wave_scan((uint64_t)g.pages), kWave - 1);
         const uint32_t token_vecs = a.fd_hv.d * a.C;
@@ -1052,19 +1070,8 @@ __global__ void __launch_bounds__(B) kvx_order_kernel(GridArgs) {
         most = __builtin_amdgcn_readfirstlane(most);
         // A team of `size` wavefronts of the XCD copies a unit, each of them
         // every size-th piece of it.
-        const uint32_t pieces = (most + kWave - 1) / kWave;
-        uint32_t size = pieces, turns = 1;
-        if (size > W / 8) {
-            uint32_t used = 0;
-            for (uint32_t s = 1; s <= 8; ++s) {
-                const uint32_t z = (pieces + s - 1) / s;
-                if (z > W) continue;
-                const uint32_t u = W / z * z;
-                if (u > used + W / 16) used = u, size = z;
-            }
-            if (used == 0) size = W;
-            turns = (pieces + size - 1) / size;
-        }
+        const uint32_t pieces = (most + kWave - 1) / kWave, size = team_size(pieces, W);
+        const uint32_t turns = pieces > size ? (pieces + size - 1) / size : 1;
         const uint32_t teams = pieces ? W / size : 1, team = pieces ? w / size : 1;
         const uint32_t p0 = w - team * size, turn = (size / 2 + size / 8) | 1;
         const int64_t n0 = units > x ? (units - x + 8ll * teams - 1) / (8ll * teams) : 0;
@@ -1342,7 +1349,8 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     a.fd_To = p.fd_To;
     a.fd_hv = make_fastdiv((uint32_t)(p.H * p.vpr));
     a.fd_L = make_fastdiv((uint32_t)p.L);
-    a.granule = kWave;
+    const uint32_t pieces = (uint32_t)(((int64_t)t.T * p.C * p.H * p.vpr + kWave - 1) / kWave);
+    a.granule = team_size(pieces, (cus + 7) / 8 * (B / kWave)) < pieces ? 0 : kWave;
     while (a.granule > 1 && a.granule / 2 * (a.fd_hv.d % kWave) % kWave == 0) a.granule /= 2;
     const bool link = p.src_host || p.dst_host;
     const int64_t page_vecs = (int64_t)t.T * p.C * p.H * p.vpr;

@@ -119,6 +119,20 @@ def test_source_pages_that_begin_inside_pieces(kvx, H, D, T):
     check(shift / zero, 1.25, f"{H} x {D}, shifted")
 
 
+def test_units_in_turns_of_several_source_pages(kvx):
+    """MLA pages of 128 tokens (144 KiB, which an XCD's wavefronts take in
+    turns) from pages of 64 tokens, against the same from 128 (at fault 1.4;
+    1.1)."""
+    D = PoolSpec(36, 1, 1, 576, T=128, N=128, e=2, layout=TOKEN)
+    S = PoolSpec(36, 1, 1, 576, T=64, N=256, e=2, layout=TOKEN)
+    halves, whole = Pools(kvx, S, D, 8, 16), Pools(kvx, D, D, 8, 16)
+    rows = halves.rows(15 * 128)
+    rows[:, 0] = np.arange(8) * 32
+    halves.tables[0] = np.random.default_rng(1).permutation(256).astype(np.int32)
+    halves, whole = least(halves.transfer(rows), whole.transfer(whole.rows(15 * 128)))
+    check(halves / whole, 1.2, "64 to 128 token pages of 1 x 576")
+
+
 @pytest.mark.parametrize("ls,ld", [(TOKEN, TOKEN), (HEAD, TOKEN), (TOKEN, HEAD)])
 def test_layered_sparse_pages(kvx, ls, ld):
     """Planned layered calls always sweep: of 256 KiB pages with 16 of 64

@@ -72,6 +72,17 @@ def test_source_pages_that_begin_inside_pieces(library, Ts, Td, H, D):
     check(wl)
 
 
+@pytest.mark.parametrize("Ts,Td", [(64, 128), (128, 128), (256, 128), (128, 96)])
+def test_units_in_turns(library, Ts, Td):
+    """Pages of 144 and 108 pieces, the first taken in turns: the product
+    library keeps their order where each lies in one source page."""
+    spec = [(0, 0, 900, None), (0, 0, 1000, None), (128 % Ts, 0, 800, None)]
+    wl = cases.transfer_case("LPCTHD", "LPCTHD", Ts, Td, seed=Ts + Td, D=576, L=32, C=1, H=1, spec=spec)
+    check(wl)
+    wl.steps[0].src_pt[1] = -1
+    check(wl)
+
+
 @pytest.mark.parametrize("n_reqs", [63, 64, 65, 1023, 1024, 1025, 2100])
 def test_many_records(library, n_reqs):
     """Around the 64 records of a wavefront and the 1024 of a workgroup, every
