@@ -74,14 +74,17 @@
 // a page of its own, and thousands of pages at once run at the memory's random
 // rate.  Teams, head-major 64 to token-major 64 token pages, 100 records of 400
 // to 800 tokens of 36 x 8 x 128: 2 per CU 3249 us, 3 3311, 4 3319; the way
-// back 3026, 3155 and 3197.  Smaller calls have more parts than teams without
-// them (200 tokens: 13.3 us), and small units fill no team (65536 records of 1
-// to 4 tokens of 2 x 2 x 64: 800 us in teams, 600 without).
+// back 3026, 3155 and 3197.  Calls of less data lie in the last-level cache, read and
+// written, and have more parts than teams without them: 4 records of 130 tokens, 153
+// MB, 36.3 us in teams, 30.6 without; 16 of 48, 226 MB, 47.4 and 44.5; 32 of 32, 302 MB,
+// 59.5 and 60.7; 48 of 40, 566 MB, 105.8 and 112.  Small units fill no team: of 128
+// vectors and less (65536 records of 1 to 4 tokens of 2 x 2 x 64) 800 us in teams, 610
+// without; of 720 (24-token pages of 3 x 80 bytes, 2.0 GB) 488 and 534.
 #ifndef KVX_TEAM_KIB
-#define KVX_TEAM_KIB 8
+#define KVX_TEAM_KIB 32
 #endif
 #ifndef KVX_TEAM_UNIT
-#define KVX_TEAM_UNIT (4 * kWave * KVX_PARTS_UNROLL)
+#define KVX_TEAM_UNIT (4 * kWave)
 #endif
 #ifndef KVX_TEAM_PARTS
 #define KVX_TEAM_PARTS 1

@@ -142,7 +142,7 @@ def test_rows_through_a_buffer(library, layout, pinned):
 @pytest.mark.parametrize("ls,ld,Ts,Td", [("PLCHTD", "LPCTHD", 64, 16), ("PLCHTD", "LPCHTD", 64, 64), ("LPCTHD", "PLCHTD", 16, 64)])
 @pytest.mark.parametrize("n_reqs", [1, 12, 80])
 def test_product_library_copies_much_data_of_rows_by_teams(ls, ld, Ts, Td, n_reqs):
-    """4000 tokens over 8 layers, 131 MB, in 1, 12 or 80 records (many or few
+    """4000 tokens over 16 layers, 262 MB, in 1, 12 or 80 records (many or few
     table entries for each), above the size from which the product library's
     wavefronts share parts; odd starts, and a bad id on each side."""
     torch = pytest.importorskip("torch")
@@ -150,8 +150,8 @@ def test_product_library_copies_much_data_of_rows_by_teams(ls, ld, Ts, Td, n_req
         pytest.skip("no GPU")
     n = 4000 // n_reqs
     per_s, per_d = -(-(n + 5) // Ts), -(-(n + 3) // Td)
-    S = PoolSpec(8, 2, 8, 128, T=Ts, N=per_s * n_reqs + 6, e=2, layout=ls)
-    D = PoolSpec(8, 2, 8, 128, T=Td, N=per_d * n_reqs + 6, e=2, layout=ld)
+    S = PoolSpec(16, 2, 8, 128, T=Ts, N=per_s * n_reqs + 6, e=2, layout=ls)
+    D = PoolSpec(16, 2, 8, 128, T=Td, N=per_d * n_reqs + 6, e=2, layout=ld)
     rng = np.random.default_rng(6)
     src = rng.permutation(S.N)[:per_s * n_reqs].astype(np.int32)
     dst = rng.permutation(D.N)[:per_d * n_reqs].astype(np.int32)
