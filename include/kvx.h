@@ -89,8 +89,8 @@ extern "C" {
 
 #define KVX_ABI_VERSION 1
 
-/* Most request records per call (each workgroup of the copy kernel reads
- * the whole record array, 256 records at a time). */
+/* Most request records per call (every workgroup of an unplanned call reads
+ * the whole record array, its wavefronts 64 records at a time). */
 #define KVX_MAX_REQS 65536
 /* Largest page (tokens) a pool may declare. */
 #define KVX_MAX_PAGE_TOKENS (1 << 20)
@@ -311,7 +311,8 @@ typedef struct kvx_plan_slot {
  * average, or 12 KiB and two thirds of a page, and both tables hold 1 to
  * INT32_MAX entries, the call can
  * sweep: one workgroup per 1 KiB piece of each destination page of each
- * layer, layer by layer and page by page, every page on one XCD, instead of
+ * layer (of its average part, where pages are less than two thirds full on
+ * average), layer by layer and page by page, every page on one XCD, instead of
  * a persistent grid.  Started in that order by the hardware, the pieces in
  * flight stay within a small window that slides through the transfer; on
  * MI355X this holds the handoff's 256 KiB pages at 6.55-6.65 TB/s and MLA's

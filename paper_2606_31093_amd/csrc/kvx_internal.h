@@ -24,21 +24,22 @@
 // A planned transfer can sweep when its records copy at least this many bytes
 // per destination page and layer on average, or at least
 // KVX_SWEEP_MIN_DENSE_BYTES and two thirds of a page.  Measured against the
-// persistent grid on the same pools, full pages, TB/s read + write: 16 KiB
-// pages 5.16 to 5.02, 64 KiB 6.07 to 5.11, 128 KiB 6.64 to 5.1.  A sweep
-// launches a page's pieces whether or not the records copy them; an empty
-// one takes two thirds of a copied one's time, so a page less than two thirds
-// full is left to the grid unless it is large (there the measured launch
-// choice decides).
+// unplanned launch on the same pools, 28 layers in groups of 4, us: full pages of
+// 16 KiB (2 x 128, 2.7 GB) 515 to 606 token-major, 533 to 590 from head-major, 562
+// to 602 into it, 576 to 605 both; of 32 KiB 1032 to 1168, 1056 to 1137, 1089 to
+// 1139, 943 to 1000; of 64 KiB 923 to 973, 935 to 1160, 861 to 1006, 925 to 1053.
+// Pages less than two thirds full get workgroups for what they hold on average
+// (kvx_sweep_kernel): 256 KiB pages of 16 and 32 tokens of 64 270 to 318 and 440 to
+// 554 us.
 #ifndef KVX_SWEEP_MIN_BYTES
 #define KVX_SWEEP_MIN_BYTES (64 << 10)
 #endif
 #ifndef KVX_SWEEP_MIN_DENSE_BYTES
 #define KVX_SWEEP_MIN_DENSE_BYTES (12 << 10)
 #endif
-// Most workgroups of one sweep launch: the work-items of a launch (64 per
-// workgroup) must stay below 2^32, and this keeps them below 2^31.  A larger
-// transfer takes several launches.
+// Most copying workgroups of one sweep launch; up to 1024 that check the plan come
+// on top in the first.  The work-items of a launch (64 per workgroup) must stay
+// below 2^32, and are at most 2^31 + 2^16.  A larger transfer takes several launches.
 #ifndef KVX_SWEEP_MAX_BLOCKS
 #define KVX_SWEEP_MAX_BLOCKS (INT32_MAX / 64)
 #endif

@@ -63,7 +63,7 @@
 #define KVX_SHARE_ROWS_BLOCKS_PER_CU 6
 #endif
 // Parts per wavefront that units are cut into.  64 half-filled pages of 36
-// layers: 108 us with 32, 116 with 8.
+// layers: 111 us with 16 to 64.
 #ifndef KVX_GRID_PARTS
 #define KVX_GRID_PARTS 32
 #endif
@@ -136,8 +136,8 @@
 #define KVX_ORDER_TURNS 16
 #endif
 // ... and, on the host, calls whose table holds this many entries per record: a
-// small call with a table longer than its records need takes 13.6 us in
-// workgroups of 1024 threads, 12.2 without.
+// small call with a table longer than its records need takes 14.2 us in
+// workgroups of 1024 threads, 12.2 without (64 decode records).
 #ifndef KVX_ORDER_PAGES
 #define KVX_ORDER_PAGES 8
 #endif
@@ -270,7 +270,8 @@ struct SweepArgs {
 // - RUNS: the copied heads of consecutive tokens are one run on both sides;
 // - TOKENS: the copied heads of a token are one run on both sides;
 // - ROWS_T: token by token into a token-major destination, rows resolved;
-// - ROWS_H: by slot blocks into a head-major destination, rows resolved.
+// - ROWS_H: by slot blocks into a head-major destination, rows resolved (the
+//   sweep takes a head range of a token-major destination the same way).
 enum SweepMode { RUNS, TOKENS, ROWS_T, ROWS_H };
 
 // A piece that the sweep's common path does not cover: rows in several source
