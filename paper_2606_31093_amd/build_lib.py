@@ -17,8 +17,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIBRARY = os.path.join(PKG, "libkvx.so")
 # The test build: its hash chain gives up after one empty poll, planned
 # transfers of any size take the sweep launch (its launch choice starts as
-# KVX_CHOOSE_SWEEP), with at most 2048 workgroups, so that larger cases take
-# several launches, unplanned runs of any size are copied in order, and
+# KVX_CHOOSE_SWEEP), with at most 2048 copying workgroups, so that larger cases
+# take several launches, unplanned runs of any size are copied in order, and
 # unplanned rows of any size by teams of wavefronts.
 # These are compile-time options: the product library has
 # no switch for them.

@@ -1,7 +1,9 @@
 """Unplanned calls, bit for bit against the oracle: runs on both sides in order
 (the test build copies every such call in order, the product library those of
 long records), rows by teams of wavefronts (the test build all of them, the
-product library those of much data), and the rest in parts."""
+product library those of much data), and the rest in parts.  The product library
+decides on the device, from the records, which of them a call takes; tests named
+for one choose sizes for which it does, and compare bytes and error bits."""
 import numpy as np
 import pytest
 

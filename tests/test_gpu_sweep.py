@@ -2,8 +2,8 @@
 against the oracle.
 
 The test build (libkvx_test.so) takes the sweep for every planned transfer
-whatever its size and destination layout, with at most 2048 workgroups per
-launch (larger cases take several launches), so small cases exercise it: every layout pair and
+whatever its size and destination layout, with at most 2048 copying workgroups
+per launch (larger cases take several launches), so small cases exercise it: every layout pair and
 page-size pair, element widths, slices, copies inside one pool, the seeded
 random cases (damaged tables, empty requests, shared source pages, slices)
 and the device error rules.  A wrong token total only changes the choice of
