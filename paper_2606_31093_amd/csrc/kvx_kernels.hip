@@ -68,23 +68,27 @@
 #define KVX_GRID_PARTS 32
 #endif
 // Unplanned calls that resolve rows: from KVX_TEAM_KIB KiB per wavefront of the
-// grid on, in units that most often hold KVX_TEAM_UNIT vectors, four wavefronts
-// share a part, and of the grid only KVX_TEAM_BLOCKS_PER_CU workgroups per CU
-// work, KVX_TEAM_PARTS parts per wavefront.  A wavefront to itself walks through
-// a page of its own, and thousands of pages at once run at the memory's random
-// rate.  Teams, head-major 64 to token-major 64 token pages, 100 records of 400
+// grid on, in units that most often hold KVX_TEAM_UNIT vectors or belong to records
+// of many pages, four wavefronts share a part, and of the grid only
+// KVX_TEAM_BLOCKS_PER_CU workgroups per CU work, KVX_TEAM_PARTS parts per wavefront.
+// A wavefront to itself walks through a page of its own, and thousands of pages at
+// once run at the memory's random rate.  Teams, head-major 64 to token-major 64 token pages, 100 records of 400
 // to 800 tokens of 36 x 8 x 128: 2 per CU 3249 us, 3 3311, 4 3319; the way
 // back 3026, 3155 and 3197.  Calls of less data lie in the last-level cache, read and
 // written, and have more parts than teams without them: 4 records of 130 tokens, 153
 // MB, 36.3 us in teams, 30.6 without; 16 of 48, 226 MB, 47.4 and 44.5; 32 of 32, 302 MB,
-// 59.5 and 60.7; 48 of 40, 566 MB, 105.8 and 112.  Small units fill no team: of 128
-// vectors and less (65536 records of 1 to 4 tokens of 2 x 2 x 64) 800 us in teams, 610
-// without; of 720 (24-token pages of 3 x 80 bytes, 2.0 GB) 488 and 534.
+// 59.5 and 60.7; 48 of 40, 566 MB, 105.8 and 112.  Small units fill no
+// team, unless they are small pages of long records (KVX_TEAM_PAGES or more of them):
+// 2000 records of 1 to 8 tokens, 4 heads of 256 bytes 376 us in teams, 268 without;
+// 24-token pages of 3 x 80 bytes, 2.0 GB, 490 and 534.
 #ifndef KVX_TEAM_KIB
 #define KVX_TEAM_KIB 32
 #endif
 #ifndef KVX_TEAM_UNIT
-#define KVX_TEAM_UNIT (4 * kWave)
+#define KVX_TEAM_UNIT 4096
+#endif
+#ifndef KVX_TEAM_PAGES
+#define KVX_TEAM_PAGES 4
 #endif
 #ifndef KVX_TEAM_PARTS
 #define KVX_TEAM_PARTS 1
@@ -786,7 +790,8 @@ struct Records {
 // Whether four wavefronts share each part, judged by 64 of the records, one per
 // lane (`chunks` times as many in all), whose largest pages hold `tile` vectors.
 __device__ __forceinline__ bool worth_teams(const GridArgs &a, const GridRec &g, uint32_t tile, uint32_t chunks) {
-    const uint64_t some = __ballot(g.pages > 0), large = __ballot(g.pages > 0 && tile >= KVX_TEAM_UNIT);
+    const uint64_t some = __ballot(g.pages > 0), large = __ballot(
+        g.pages > 0 && (tile >= KVX_TEAM_UNIT || (g.pages >= KVX_TEAM_PAGES && tile >= 4 * kWave)));
     const uint64_t all = (uint64_t)lane64(wave_scan((uint64_t)g.pages * tile), kWave - 1) * a.fd_L.d * chunks;
     return all >= a.team_min && 2 * __builtin_popcountll(large) >= __builtin_popcountll(some);
 }

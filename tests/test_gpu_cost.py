@@ -153,3 +153,17 @@ def test_layered_sparse_pages(kvx, ls, ld):
         kvx.kvx_transfer_layered(p.mem[0], S, p.mem[1], D, spt, dpt, reqs, 4, events)
     a, b = least(planned, unplanned)
     check(a / b, 1.1, f"{ls} -> {ld}, 16 of 64 tokens a page")
+
+
+@pytest.mark.parametrize("ls,ld", [(HEAD, TOKEN), (TOKEN, HEAD), (HEAD, HEAD)])
+def test_short_records_of_rows(kvx, ls, ld):
+    """2048 records of 6 tokens whose rows are resolved, against the same
+    records between token-major pools (at fault
+    1.04 to 1.11; 0.89 to 0.95)."""
+    def call(ls, ld):
+        S, D = (PoolSpec(36, 2, 4, 128, T=64, N=256, e=2, layout=x) for x in (ls, ld))
+        p = Pools(kvx, S, D, 256, 1)
+        r = np.arange(2048)
+        return p.transfer(np.stack([r // 8, r // 8, 0 * r, r % 8 * 8, r % 8 * 8, 0 * r + 6], axis=1))
+    rows, runs = least(call(ls, ld), call(TOKEN, TOKEN))
+    check(rows / runs, 1.0, f"{ls} -> {ld}, short records")
