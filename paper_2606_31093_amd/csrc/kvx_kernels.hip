@@ -534,6 +534,7 @@ struct GridArgs {
     FastDiv fd_Tt, fd_To, fd_hv, fd_L;
     uint32_t granule;                 // tokens after which a whole number of 64 vectors ends; 0: full units in turns
     uint32_t t_h, o_h;                // rows only
+    uint32_t slot_shift;              // ROWS_H: log2 of the slots per block
     FastDiv fd_vpr, fd_H;             // rows only
     uint64_t team_min;                // rows only: vectors from which teams of wavefronts share a part,
     uint32_t team_blocks;             // and the workgroups that then work
@@ -651,22 +652,20 @@ struct GridPart {
 };
 
 // Slots that a unit's vectors enumerate: its tokens, or (ROWS_H) the whole
-// blocks of KVX_SLOT_BLOCK slots that they meet.
+// blocks of 1 << sb slots that they meet.
 template <SweepMode MODE>
-__device__ __forceinline__ uint32_t unit_slots(uint32_t sa, uint32_t ntok) {
-    constexpr uint32_t SB = KVX_SLOT_BLOCK;
-    return MODE == ROWS_H ? ((sa + ntok - 1) / SB - sa / SB + 1) * SB : ntok;
+__device__ __forceinline__ uint32_t unit_slots(uint32_t sa, uint32_t ntok, uint32_t sb) {
+    return MODE == ROWS_H ? (((sa + ntok - 1) >> sb) - (sa >> sb) + 1) << sb : ntok;
 }
 
 // The most of them that a page of a record has.
 template <SweepMode MODE>
-__device__ __forceinline__ uint32_t record_slots(const GridRec &g, uint32_t T) {
-    constexpr uint32_t SB = KVX_SLOT_BLOCK;
+__device__ __forceinline__ uint32_t record_slots(const GridRec &g, uint32_t T, uint32_t sb) {
     if (g.pages == 0) return 0;
     const uint32_t n = (uint32_t)g.n < T ? (uint32_t)g.n : T;
     if (MODE != ROWS_H) return n;
-    const uint32_t some = (n - 1) / SB + 2, all = (T - 1) / SB + 1;
-    return (some < all ? some : all) * SB;
+    const uint32_t some = ((n - 1) >> sb) + 2, all = ((T - 1) >> sb) + 1;
+    return (some < all ? some : all) << sb;
 }
 
 // Token (from the unit's first one; out of range for a masked slot), head and
@@ -674,12 +673,11 @@ __device__ __forceinline__ uint32_t record_slots(const GridRec &g, uint32_t T) {
 template <SweepMode MODE>
 __device__ __forceinline__ void unit_row(const GridArgs &a, uint32_t sa, uint32_t w, uint32_t &tok, uint32_t &h,
                                          uint32_t &v) {
-    constexpr uint32_t SB = KVX_SLOT_BLOCK;
     if (MODE == ROWS_H) {
-        const uint32_t rw = fd_div(a.fd_vpr, w), q1 = rw / SB, blk = fd_div(a.fd_H, q1);
+        const uint32_t sb = a.slot_shift, rw = fd_div(a.fd_vpr, w), q1 = rw >> sb, blk = fd_div(a.fd_H, q1);
         v = w - rw * a.fd_vpr.d;
         h = q1 - blk * a.fd_H.d;
-        tok = (sa / SB + blk) * SB + (rw - q1 * SB) - sa;
+        tok = (((sa >> sb) + blk) << sb) + (rw - (q1 << sb)) - sa;
     } else {
         tok = fd_div(a.fd_hv, w);
         v = w - tok * a.fd_hv.d;
@@ -829,7 +827,7 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
         const GridArgs &a = fresh_args();
         GridRec g;
         (void)grid_record<OP>(a, load_raw(a, lane), g);
-        const uint32_t tile = record_slots<MODE>(g, a.fd_Tt.d) * a.fd_hv.d * a.C;
+        const uint32_t tile = record_slots<MODE>(g, a.fd_Tt.d, a.slot_shift) * a.fd_hv.d * a.C;
         if (worth_teams(a, g, tile, (n_reqs + kWave - 1) / kWave)) {
             if (blockIdx.x >= a.team_blocks) return;
             workers = a.team_blocks * kWaves;
@@ -844,7 +842,7 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
         GridRec g;                                         // (a lane without a record has an empty one)
         const uint32_t bad = grid_record<OP>(ra, load_raw(ra, r0 + (SHARE ? threadIdx.x : lane)), g);
         if (bad && blockIdx.x == 0 && (SHARE || wave == 0) && ra.err) atomicOr(ra.err, bad);
-        const uint32_t tile = record_slots<MODE>(g, T) * ra.fd_hv.d * ra.C;   // vectors of the record's largest page
+        const uint32_t tile = record_slots<MODE>(g, T, ra.slot_shift) * ra.fd_hv.d * ra.C;   // vectors of the record's largest page
         if (!SHARE && kRows && worth_teams(ra, g, tile, 1)) {
             if (blockIdx.x >= ra.team_blocks) return;
             workers = ra.team_blocks * kWaves;
@@ -910,7 +908,7 @@ __device__ __forceinline__ void copy_parts(Records<B> *shared) {
                 w.o_off = lane64(g.o_off, r);
                 w.sa = sa;
                 w.ntok = ntok;
-                w.R = unit_slots<MODE>(sa, ntok) * a.fd_hv.d;
+                w.R = unit_slots<MODE>(sa, ntok, a.slot_shift) * a.fd_hv.d;
                 const uint32_t vecs = w.R * a.C;
                 const uint32_t size = lane32(part_vecs, r);
                 w.kb = part * size;
@@ -974,11 +972,14 @@ __global__ void __launch_bounds__(kBlock) kvx_parts_kernel(GridArgs) {
     copy_parts<OP, MODE, HOST, U, kBlock, false>(nullptr);
 }
 
-// The same for more than 64 records.
+// The same for more than 64 records.  (Six wavefronts per SIMD: with 81 registers for
+// head-major rows it had five, 4000 records of 1-8 tokens 1139 us : 1039.)
 template <SweepMode MODE>
 constexpr int kShareBlock = MODE == ROWS_T || MODE == ROWS_H ? kBlock : KVX_SHARE_BLOCK;
 template <int OP, SweepMode MODE, bool HOST, int U>
-__global__ void __launch_bounds__(kShareBlock<MODE>) kvx_shared_parts_kernel(GridArgs) {
+__global__ void __launch_bounds__(kShareBlock<MODE>, MODE == ROWS_H && U == KVX_PARTS_UNROLL
+                                                         ? KVX_SHARE_ROWS_BLOCKS_PER_CU : 1)
+kvx_shared_parts_kernel(GridArgs) {
     __shared__ Records<kShareBlock<MODE>> shared;
     copy_parts<OP, MODE, HOST, U, kShareBlock<MODE>, true>(&shared);
 }
@@ -1296,6 +1297,23 @@ hipError_t device_cus(int *cus) {
     return q;
 }
 
+// log2 of the slots per block of a head-major tiling side's vector order: blocks
+// of KVX_SLOT_BLOCK slots, and of rows narrower than a 128-byte line as many more
+// as end with one, up to 8.  A page's narrow rows are written by several
+// wavefronts, and a line whose halves come from two of them is written twice.
+// 17 records of 900-1100 tokens, 330 MB, blocks of 2 and of 8 (4 for 96 bytes), us:
+// 8 heads of 48 bytes 87 and 48, of 80 bytes 126 and 70, 5 of 112 bytes 105 and 70, 5 of
+// 96 bytes 75 and 67; a workgroup per page, blocks of 2, took 65, 93, 89 and 71.  With
+// rows of whole lines larger blocks only add masked slots to short records (2000 of
+// 1-4 tokens, 8 heads of 256 bytes: 305 us with blocks of 2, 361 of 4, 556 of 8).
+static uint32_t slot_shift(const Params &p, int32_t T) {
+    uint32_t sb = (uint32_t)__builtin_ctz(KVX_SLOT_BLOCK);
+    while (p.row_bytes < 128 && sb < 3 && ((p.row_bytes << sb) & 127)) ++sb;
+    // (a page's vectors, whole blocks of them, are numbered with 31 bits)
+    const int64_t slots = ((((int64_t)T - 1) >> sb) + 1) << sb;
+    return slots * p.C * p.H * p.vpr <= INT32_MAX ? sb : (uint32_t)__builtin_ctz(KVX_SLOT_BLOCK);
+}
+
 // The launch of an unplanned call.
 template <int OP>
 static int launch_grid(const Params &p, hipStream_t stream) {
@@ -1352,6 +1370,7 @@ static int launch_grid(const Params &p, hipStream_t stream) {
     }
     a.t_h = (uint32_t)(t.s_h / 16);
     a.o_h = OP == OP_TRANSFER ? (uint32_t)(o.s_h / 16) : (uint32_t)p.vpr;
+    a.slot_shift = slot_shift(p, t.T);
     a.fd_vpr = p.fd_vpr;
     a.fd_H = p.fd_H;
     a.fd_Tt = p.fd_Tt;

@@ -167,3 +167,16 @@ def test_short_records_of_rows(kvx, ls, ld):
         return p.transfer(np.stack([r // 8, r // 8, 0 * r, r % 8 * 8, r % 8 * 8, 0 * r + 6], axis=1))
     rows, runs = least(call(ls, ld), call(TOKEN, TOKEN))
     check(rows / runs, 1.0, f"{ls} -> {ld}, short records")
+
+
+@pytest.mark.parametrize("H,D", [(8, 80), (5, 112), (8, 48)])
+def test_rows_narrower_than_a_line(kvx, H, D):
+    """Head-major rows that are no whole 128-byte lines, against 64-byte rows of
+    the same data (at fault 1.5 to 1.8; 1.0)."""
+    def call(H, D, L):
+        S = PoolSpec(L, 2, H, D, T=64, N=288, e=1, layout=HEAD)
+        p = Pools(kvx, S, S, 17, 16)
+        return p.transfer(p.rows(1000)), L * H * D
+    (narrow, n), (even, m) = call(H, D, 5120 // (H * D)), call(8, 64, 10)
+    a, b = least(narrow, even)
+    check(a / n / (b / m), 1.2, f"{H} x {D} bytes")

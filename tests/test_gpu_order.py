@@ -135,6 +135,16 @@ def test_rows(library, ls, ld, H, D, L, Ts, Td):
     check(cases.transfer_case(ls, ld, Ts, Td, seed=Ts + 3 * Td + H, D=D, L=L, H=H, spec=spec))
 
 
+@pytest.mark.parametrize("Ts,Td", [(16, 64), (64, 13), (7, 7)])
+@pytest.mark.parametrize("H,D", [(3, 16), (2, 32), (8, 48), (1, 64), (5, 80), (4, 96), (3, 112)])
+@pytest.mark.parametrize("ls,ld", [("LPCTHD", "LPCHTD"), ("PLCHTD", "LPCHTD")])
+def test_narrow_rows(library, ls, ld, H, D, Ts, Td):
+    """Rows narrower than a 128-byte line, which a head-major destination takes in
+    blocks of 2 to 8 slots: blocks masked at both ends, pages that end inside one."""
+    spec = [(1, 3, 1, None), (0, 0, 0, None), (Ts - 1, Td - 1, 2 * Td + 3, None), (0, 1, Ts, None), (2, 5, 3 * Ts + 9, None)]
+    check(cases.transfer_case(ls, ld, Ts, Td, seed=Ts + 3 * Td + H, e=1, D=D, L=3, H=H, spec=spec))
+
+
 @pytest.mark.parametrize("pinned", [False, True])
 @pytest.mark.parametrize("layout", ["LPCHTD", "PLCHTD"])
 def test_rows_through_a_buffer(library, layout, pinned):
